@@ -247,10 +247,10 @@ def _inputs(case, seed):
         p["opacity"] = torch.where(torch.rand(n, generator=g, device="cuda") < 0.02,
                                    torch.full_like(p["opacity"], 0.003), p["opacity"]).clamp_min(0.003)
         out["m"], out["v"] = _moments(p, 1e-6, g)
-        out["rand"] = torch.randint(0, 2 ** 32, (n,), generator=g, dtype=torch.int64, device="cuda").to(torch.int32)
-        out["rand_add"] = torch.randint(0, 2 ** 32, (n,), generator=g, dtype=torch.int64,
-                                        device="cuda").to(torch.int32)
-        out["normals"] = torch.randn(n, 3, generator=g, device="cuda")
+        add = int(case["grow"] * n)
+        words = lambda k: torch.randint(0, 2 ** 32, (k,), generator=g, dtype=torch.int64, device="cuda").to(torch.int32)
+        out["rand"], out["rand_add"] = words(n + add), words(max(add, 1))
+        out["normals"] = torch.randn(n + add, 3, generator=g, device="cuda")
     else:
         out["m"], out["v"] = _moments(p, 1e-6, g)
         # fixed shares, in random places: 5% cloned, 5% split, 8% transparent
@@ -282,14 +282,7 @@ def prepare(case, seed):
         st["ws"] = torch.empty(L.linprim_loss_workspace_size(st["cams_c"]), dtype=torch.uint8, device="cuda")
         st["grad"] = torch.empty_like(inp["rgb"])
         return st
-    if task == "mcmc":
-        n, add = case["n"], int(case["grow"] * case["n"])
-        grow = lambda t: torch.cat([t, torch.zeros((add,) + tuple(t.shape[1:]), device="cuda")])
-        for key in ("params", "m", "v"):
-            st[key] = {k: grow(t) for k, t in inp[key].items()}
-        st["mcmc"] = MCMC(n, case["sh_degree"])
-        return st
-    if task == "densify":
+    if task in ("mcmc", "densify"):
         return st
     kind = _kind(case)
     prims = L.Prims(kind, *(inp["params"][k] for k in FIELDS), sh_degree=case["sh_degree"])
@@ -388,11 +381,13 @@ def _run_train(state):
 
 
 def _run_mcmc(state):
+    # growth first (new arrays), then relocation and noise in place on them:
+    # the state's own arrays stay as they are
     case = state["case"]
-    mc, p, m, v = state["mcmc"], state["params"], state["m"], state["v"]
+    mc = MCMC(case["n"], case["sh_degree"])
+    p, m, v = mc.add(state["params"], int(case["grow"] * case["n"]), state["m"], state["v"],
+                     rand_u32=state["rand_add"])
     mc.relocate(p, m, v, rand_u32=state["rand"])
-    L.linprim_mcmc_add(L.OCTAHEDRON, case["sh_degree"], case["n"], int(case["grow"] * case["n"]), L.state(p, m, v),
-                       state["rand_add"], mc.ws)
     mc.noise(p, 1e-4, normals=state["normals"])
     return {"p": p, "m": m, "v": v}
 
@@ -417,10 +412,10 @@ def work(case):
     n = case["n"]
     if task == "mcmc":
         add = int(case["grow"] * n)
-        # opacities and randoms read, the noised means, the copied rows with
-        # their moments (2% relocated, the added ones)
+        # every row with its moments moved into the grown arrays, the copied
+        # rows (added, and 2% relocated), randoms and noise
         rows = add + n // 50
-        return {"bytes": n * 4 * (2 + 1 + 11 + 6) + rows * 4 * 8 * words, "flops": 150 * n}
+        return {"bytes": n * 4 * 6 * words + rows * 4 * 5 * words + n * 4 * 5, "flops": 150 * n}
     if task == "densify":
         return {"bytes": n * 4 * (6 * words + 3), "flops": 20 * n}
     if case["width"]:
@@ -770,16 +765,16 @@ def _exact_mcmc(case, inp):
                                                         device="cuda")])
     p, m, v = ({k: grow(t) for k, t in inp[key].items()} for key in ("params", "m", "v"))
     op = p["opacity"][:n].float()
+    _relocate64(p, m, v, _draws(op, inp["rand_add"], add), torch.arange(n, n + add, device="cuda"))
+    op = p["opacity"].float()
     dead = torch.nonzero(op <= 0.005)[:, 0]
     _relocate64(p, m, v, _draws(op, inp["rand"], dead.numel()), dead)
-    op = p["opacity"][:n].float()
-    _relocate64(p, m, v, _draws(op, inp["rand_add"], add), torch.arange(n, n + add, device="cuda"))
-    gate = 1 / (1 + torch.exp(-100 * ((1 - p["opacity"][:n]) - 0.995)))
-    R = _rotation(p["quats"][:n])
+    gate = 1 / (1 + torch.exp(-100 * ((1 - p["opacity"]) - 0.995)))
+    R = _rotation(p["quats"])
     e = torch.matmul(R.transpose(1, 2), inp["normals"].double()[:, :, None])[:, :, 0]
-    e = torch.matmul(R, (e * (p["dists"][:n] / 2.6) ** 2)[:, :, None])[:, :, 0]
+    e = torch.matmul(R, (e * (p["dists"] / 2.6) ** 2)[:, :, None])[:, :, 0]
     lr = float(torch.tensor(1e-4, dtype=torch.float32))
-    p["means"][:n] += 5e5 * lr * gate[:, None] * e
+    p["means"] += 5e5 * lr * gate[:, None] * e
     return {"p": p, "m": m, "v": v}
 
 
