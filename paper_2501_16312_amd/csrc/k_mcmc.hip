@@ -6,8 +6,10 @@
 //   k_mc_count    per block of 1,024: sums of the integer weights
 //                 w_i = floor(alpha_i 2^32) of live primitives (alpha > 0.005)
 //                 and of the dead flags;
-//   k_mc_scan     exclusive scan of both block sums (one block);
+//   k_mc_scan     exclusive scan of both block sums (one block; only beyond
+//                 kMcDirectBlocks blocks);
 //   k_mc_prefix   inclusive weight prefix per primitive, list of the dead;
+//                 each block adds the sums of the blocks before it itself;
 //   k_mc_sample   the k-th dead primitive draws a source: the first index whose
 //                 prefix exceeds floor(total r_k / 2^32) (binary search);
 //                 per-source draw counts by integer atomics;
@@ -24,6 +26,10 @@ namespace linprim {
 constexpr float kMcDead = 0.005f;
 constexpr int kMcItems = 1024;
 constexpr int kMcMaxN = 51;
+// Up to this many blocks of kMcItems primitives, each block of k_mc_prefix
+// adds the sums of the blocks before it (8 KB of loads per block and sum at
+// 1M primitives, from L2) instead of waiting for a one-block scan kernel.
+constexpr int64_t kMcDirectBlocks = 8192;
 
 __device__ inline uint64_t mc_weight(float a) {
     return a > kMcDead ? (uint64_t)floor((double)a * 4294967296.0) : 0ull;
@@ -106,19 +112,37 @@ __global__ __launch_bounds__(1024) void k_mc_scan(uint64_t* __restrict__ wsum, i
     }
 }
 
-__global__ __launch_bounds__(256) void k_mc_prefix(int64_t n, const float* __restrict__ opacity,
-                                                   const uint64_t* __restrict__ wsum,
-                                                   const int64_t* __restrict__ dsum, uint64_t* __restrict__ prefix,
-                                                   int32_t* __restrict__ dead_list, int32_t* __restrict__ counts) {
+// Sum of a u64 over the 64 lanes of a wave (every lane gets it).
+__device__ inline uint64_t mc_wave_sum(uint64_t x) {
+    for (int off = 32; off >= 1; off >>= 1) x += __shfl_xor(x, off, 64);
+    return x;
+}
+
+// `scanned`: wsum and dsum hold exclusive prefixes and their totals
+// (k_mc_scan); otherwise the blocks' own sums, and the last block writes the
+// totals after them.
+__global__ __launch_bounds__(256) void k_mc_prefix(int64_t n, const float* __restrict__ opacity, bool scanned,
+                                                   uint64_t* __restrict__ wsum, int64_t* __restrict__ dsum,
+                                                   uint64_t* __restrict__ prefix, int32_t* __restrict__ dead_list,
+                                                   int32_t* __restrict__ counts) {
     constexpr int PER = kMcItems / 256;
-    __shared__ uint64_t sw[256];
-    __shared__ int64_t sd[256];
-    const int t = threadIdx.x;
-    const int64_t i0 = (int64_t)blockIdx.x * kMcItems + (int64_t)t * PER;
+    __shared__ uint64_t part[4][4];   // weights and dead of the blocks before; of this block's waves
+    const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+    const int64_t b = blockIdx.x;
+    const int64_t i0 = b * kMcItems + (int64_t)t * PER;
+    uint64_t bw = 0, bd = 0;
+    if (!scanned) {
+        for (int64_t k = t; k < b; k += 256) {
+            bw += wsum[k];
+            bd += (uint64_t)dsum[k];
+        }
+        bw = mc_wave_sum(bw);
+        bd = mc_wave_sum(bd);
+    }
     uint64_t w[PER];
     bool dead[PER];
     uint64_t mw = 0;
-    int64_t md = 0;
+    uint32_t md = 0;
 #pragma unroll
     for (int k = 0; k < PER; ++k) {
         const int64_t i = i0 + k;
@@ -126,21 +150,41 @@ __global__ __launch_bounds__(256) void k_mc_prefix(int64_t n, const float* __res
         w[k] = i < n ? mc_weight(a) : 0ull;
         dead[k] = i < n && a <= kMcDead;
         mw += w[k];
-        md += dead[k] ? 1 : 0;
+        md += dead[k] ? 1u : 0u;
     }
-    sw[t] = mw;
-    sd[t] = md;
+    uint64_t iw = mw;
+    for (int off = 1; off < 64; off <<= 1) {
+        const uint64_t y = __shfl_up(iw, off, 64);
+        if (lane >= off) iw += y;
+    }
+    const uint32_t id = wave_incl_scan_u32(md);
+    if (lane == 63) {
+        part[0][wave] = bw;
+        part[1][wave] = bd;
+        part[2][wave] = iw;
+        part[3][wave] = id;
+    }
     __syncthreads();
-    for (int off = 1; off < 256; off <<= 1) {
-        const uint64_t yw = t >= off ? sw[t - off] : 0;
-        const int64_t yd = t >= off ? sd[t - off] : 0;
-        __syncthreads();
-        sw[t] += yw;
-        sd[t] += yd;
-        __syncthreads();
+    uint64_t run, rank;
+    if (scanned) {
+        run = wsum[b];
+        rank = (uint64_t)dsum[b];
+    } else {
+        run = part[0][0] + part[0][1] + part[0][2] + part[0][3];
+        rank = part[1][0] + part[1][1] + part[1][2] + part[1][3];
+        if (b == (int64_t)gridDim.x - 1 && t == 0) {
+            wsum[b + 1] = run + part[2][0] + part[2][1] + part[2][2] + part[2][3];
+            dsum[b + 1] = (int64_t)(rank + part[3][0] + part[3][1] + part[3][2] + part[3][3]);
+        }
     }
-    uint64_t run = wsum[blockIdx.x] + sw[t] - mw;
-    int64_t rank = dsum[blockIdx.x] + sd[t] - md;
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+        if (k < wave) {
+            run += part[2][k];
+            rank += part[3][k];
+        }
+    run += iw - mw;
+    rank += id - md;
 #pragma unroll
     for (int k = 0; k < PER; ++k) {
         const int64_t i = i0 + k;
@@ -174,58 +218,141 @@ __global__ __launch_bounds__(256) void k_mc_sample(int64_t n, const uint64_t* __
     atomicAdd(counts + lo, 1);
 }
 
-__device__ inline void zero_moments(const StateSet& S, const int width[5], int64_t i) {
-    if (!S.m[0]) return;
+// Rows of one field of W words, by the whole block: row to[r] receives the
+// words of row from[r] (skipped if from is null) and its moments become zero.
+// Consecutive threads take consecutive words, four at a time where the rows
+// are whole 16-byte units and the arrays aligned.  to and from in LDS; no row
+// is both written and read.
+template <int W, int U>
+__device__ inline void mc_rows_u(float* __restrict__ p, float* __restrict__ m, float* __restrict__ v,
+                                 const int32_t* __restrict__ from, const int32_t* __restrict__ to, int R) {
+    struct alignas(4 * U) Unit {
+        float w[U];
+    };
+    constexpr int UPR = W / U;
+    Unit* P = reinterpret_cast<Unit*>(p);
+    Unit* M = reinterpret_cast<Unit*>(m);
+    Unit* V = reinterpret_cast<Unit*>(v);
+    Unit zero;
 #pragma unroll
-    for (int f = 0; f < 5; ++f)
-        for (int k = 0; k < width[f]; ++k) {
-            S.m[f][i * width[f] + k] = 0.0f;
-            S.v[f][i * width[f] + k] = 0.0f;
-        }
-}
-
-__global__ __launch_bounds__(256) void k_mc_sources(int64_t n, StateSet S, int sh_floats,
-                                                    const int32_t* __restrict__ counts) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n || counts[i] == 0) return;
-    const int N = min(counts[i] + 1, kMcMaxN);
-    const double a = (double)S.p[3][i];
-    double an = 1.0 - pow(1.0 - a, 1.0 / (double)N);
-    an = fmin(fmax(an, (double)kMcDead), 1.0 - 1.1920928955078125e-7);
-    // sum_{j=1}^{N} sum_{k=0}^{j-1} C(j-1, k) (-1)^k an^(k+1) / sqrt(k+1)
-    double denom = 0.0;
-    for (int j = 1; j <= N; ++j) {
-        double c = 1.0;                       // C(j-1, k)
-        double p = an;                        // an^(k+1)
-        for (int k = 0; k < j; ++k) {
-            denom += ((k & 1) ? -c : c) * p / sqrt((double)(k + 1));
-            c = c * (double)(j - 1 - k) / (double)(k + 1);
-            p *= an;
+    for (int k = 0; k < U; ++k) zero.w[k] = 0.0f;
+    for (int j = threadIdx.x; j < R * UPR; j += 256) {
+        const int r = j / UPR, q = j - r * UPR;
+        const int64_t d = (int64_t)to[r] * UPR + q;
+        if (from) P[d] = P[(int64_t)from[r] * UPR + q];
+        if (m) {
+            M[d] = zero;
+            V[d] = zero;
         }
     }
-    const double coeff = a / denom;
+}
+
+template <int W>
+__device__ inline void mc_rows(const StateSet& S, int f, const int32_t* from, const int32_t* to, int R) {
+    const uintptr_t a = reinterpret_cast<uintptr_t>(S.p[f]) | reinterpret_cast<uintptr_t>(S.m[f]) |
+                        reinterpret_cast<uintptr_t>(S.v[f]);
+    if (W % 4 == 0 && (a & 15) == 0)
+        mc_rows_u<W, (W % 4 == 0 ? 4 : 1)>(S.p[f], S.m[f], S.v[f], from, to, R);
+    else
+        mc_rows_u<W, 1>(S.p[f], S.m[f], S.v[f], from, to, R);
+}
+
+template <int SHF>
+__device__ inline void mc_all_rows(const StateSet& S, const int32_t* from, const int32_t* to, int R) {
+    mc_rows<SHF>(S, 4, from, to, R);
+    mc_rows<4>(S, 1, from, to, R);
+    mc_rows<3>(S, 0, from, to, R);
+    mc_rows<3>(S, 2, from, to, R);
+    mc_rows<1>(S, 3, from, to, R);
+}
+
+// One block per kMcItems primitives: the drawn ones are listed in LDS, so
+// that a few full waves run the update of the few that were drawn, and all
+// threads then clear their moments along the rows' words.  (A thread per
+// primitive, clearing 118 words by itself: 40 us for 50k sources of 1M, bound
+// by the stores of single lanes; now 16 us.)
+template <int SHF>
+__global__ __launch_bounds__(256) void k_mc_sources(int64_t n, StateSet S, const int32_t* __restrict__ counts) {
+    __shared__ int32_t list[kMcItems];
+    __shared__ int32_t drawn[kMcItems];
+    __shared__ int32_t total;
+    if (threadIdx.x == 0) total = 0;
+    __syncthreads();
+    for (int k = 0; k < kMcItems / 256; ++k) {
+        const int64_t i = (int64_t)blockIdx.x * kMcItems + k * 256 + threadIdx.x;
+        const int32_t c = i < n ? counts[i] : 0;
+        if (c) {
+            const int32_t at = atomicAdd(&total, 1);   // any order: rows are independent
+            list[at] = (int32_t)i;
+            drawn[at] = c;
+        }
+    }
+    __syncthreads();
+    const int R = total;
+    for (int r = threadIdx.x; r < R; r += 256) {
+        const int64_t i = list[r];
+        const int N = min(drawn[r] + 1, kMcMaxN);
+        const double a = (double)S.p[3][i];
+        double an = 1.0 - pow(1.0 - a, 1.0 / (double)N);
+        an = fmin(fmax(an, (double)kMcDead), 1.0 - 1.1920928955078125e-7);
+        // sum_{j=1}^{N} sum_{k=0}^{j-1} C(j-1, k) (-1)^k an^(k+1) / sqrt(k+1)
+        double denom = 0.0;
+        if (N <= 32) {
+            // the sum over j first: sum_{j=k+1}^{N} C(j-1, k) = C(N, k+1).  N
+            // terms instead of N (N + 1) / 2, and as exact up to this N (3e-9
+            // of the sum at worst, an at its upper bound, either way)
+            double c = (double)N;                     // C(N, k+1), exact in double
+            double p = an;                            // an^(k+1)
+            for (int k = 0; k < N; ++k) {
+                denom += ((k & 1) ? -c : c) * p / sqrt((double)(k + 1));
+                c = c * (double)(N - 1 - k) / (double)(k + 2);
+                p *= an;
+            }
+        } else {
+            // beyond, the terms of the single sum cancel worse than those of
+            // the row sums (6e-3 against 1e-3 at N = 51)
+            for (int j = 1; j <= N; ++j) {
+                double c = 1.0;                       // C(j-1, k)
+                double p = an;                        // an^(k+1)
+                for (int k = 0; k < j; ++k) {
+                    denom += ((k & 1) ? -c : c) * p / sqrt((double)(k + 1));
+                    c = c * (double)(j - 1 - k) / (double)(k + 1);
+                    p *= an;
+                }
+            }
+        }
+        const double coeff = a / denom;
 #pragma unroll
-    for (int k = 0; k < 3; ++k) S.p[2][i * 3 + k] = (float)((double)S.p[2][i * 3 + k] * coeff);
-    S.p[3][i] = (float)an;
-    const int width[5] = {3, 4, 3, 1, sh_floats};
-    zero_moments(S, width, i);
+        for (int k = 0; k < 3; ++k) S.p[2][i * 3 + k] = (float)((double)S.p[2][i * 3 + k] * coeff);
+        S.p[3][i] = (float)an;
+    }
+    if (S.m[0]) mc_all_rows<SHF>(S, nullptr, list, R);
 }
 
 // Draw k's target: the k-th dead primitive, or row append_base + k when
-// adding (n_draws >= 0).
-__global__ __launch_bounds__(256) void k_mc_copy(StateSet S, int sh_floats, const int64_t* __restrict__ dtotal,
-                                                 int64_t n_draws, int64_t append_base,
-                                                 const uint64_t* __restrict__ wtotal,
+// adding (n_draws >= 0).  A block copies kMcCopyRows rows at a time, all
+// threads along the rows' words (54 us for 50k rows of degree 3 with moments
+// when each thread copied a whole row; now 18 us).
+constexpr int kMcCopyRows = 64;
+template <int SHF>
+__global__ __launch_bounds__(256) void k_mc_copy(StateSet S, const int64_t* __restrict__ dtotal, int64_t n_draws,
+                                                 int64_t append_base, const uint64_t* __restrict__ wtotal,
                                                  const int32_t* __restrict__ dead_list,
                                                  const int32_t* __restrict__ samples) {
-    const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= (n_draws >= 0 ? n_draws : *dtotal) || *wtotal == 0) return;
-    const int64_t j = n_draws >= 0 ? append_base + k : (int64_t)dead_list[k], s = samples[k];
-    const int width[5] = {3, 4, 3, 1, sh_floats};
-#pragma unroll
-    for (int f = 0; f < 5; ++f)
-        for (int q = 0; q < width[f]; ++q) S.p[f][j * width[f] + q] = S.p[f][s * width[f] + q];
-    zero_moments(S, width, j);
+    __shared__ int32_t from[kMcCopyRows], to[kMcCopyRows];
+    const int64_t total = n_draws >= 0 ? n_draws : *dtotal;
+    if (*wtotal == 0) return;
+    for (int64_t k0 = (int64_t)blockIdx.x * kMcCopyRows; k0 < total; k0 += (int64_t)gridDim.x * kMcCopyRows) {
+        const int R = (int)min((int64_t)kMcCopyRows, total - k0);
+        if ((int)threadIdx.x < R) {
+            const int64_t k = k0 + threadIdx.x;
+            from[threadIdx.x] = samples[k];
+            to[threadIdx.x] = n_draws >= 0 ? (int32_t)(append_base + k) : dead_list[k];
+        }
+        __syncthreads();
+        mc_all_rows<SHF>(S, from, to, R);
+        __syncthreads();
+    }
 }
 
 __global__ __launch_bounds__(256) void k_mc_noise(int64_t n, float* __restrict__ means,
@@ -287,17 +414,28 @@ hipError_t launch_mc_relocate(int64_t n, int64_t n_add, int sh_degree, const Sta
     int32_t* dead = (int32_t*)(ws + L.dead);
     int32_t* samples = (int32_t*)(ws + L.samples);
     int32_t* counts = (int32_t*)(ws + L.counts);
-    const int shf = 3 * (sh_degree + 1) * (sh_degree + 1);
-    const unsigned g1 = (unsigned)((n + 255) / 256);
     hipLaunchKernelGGL(k_mc_count, dim3((unsigned)nb), dim3(256), 0, s, n, S.p[3], wsum, dsum);
-    hipLaunchKernelGGL(k_mc_scan, dim3(1), dim3(1024), 0, s, wsum, dsum, nb);
-    hipLaunchKernelGGL(k_mc_prefix, dim3((unsigned)nb), dim3(256), 0, s, n, S.p[3], wsum, dsum, prefix, dead, counts);
-    const int64_t draws_max = n_add >= 0 ? n_add : n;
-    const unsigned gd = (unsigned)((draws_max + 255) / 256);
-    hipLaunchKernelGGL(k_mc_sample, dim3(gd), dim3(256), 0, s, n, prefix, wsum + nb, dsum + nb, n_add, rnd, samples,
+    const bool scanned = nb > kMcDirectBlocks;
+    if (scanned) hipLaunchKernelGGL(k_mc_scan, dim3(1), dim3(1024), 0, s, wsum, dsum, nb);
+    hipLaunchKernelGGL(k_mc_prefix, dim3((unsigned)nb), dim3(256), 0, s, n, S.p[3], scanned, wsum, dsum, prefix, dead,
                        counts);
-    hipLaunchKernelGGL(k_mc_sources, dim3(g1), dim3(256), 0, s, n, S, shf, counts);
-    hipLaunchKernelGGL(k_mc_copy, dim3(gd), dim3(256), 0, s, S, shf, dsum + nb, n_add, n, wsum + nb, dead, samples);
+    const int64_t draws_max = n_add >= 0 ? n_add : n;
+    hipLaunchKernelGGL(k_mc_sample, dim3((unsigned)((draws_max + 255) / 256)), dim3(256), 0, s, n, prefix, wsum + nb,
+                       dsum + nb, n_add, rnd, samples, counts);
+    // the blocks stride over the rows: of a relocation only the device knows how many
+    const int64_t cb = (draws_max + kMcCopyRows - 1) / kMcCopyRows;
+    const unsigned copy_blocks = (unsigned)(cb < 2048 ? cb : 2048);
+#define LP_MC(SHF_)                                                                                             \
+    hipLaunchKernelGGL(k_mc_sources<SHF_>, dim3((unsigned)nb), dim3(256), 0, s, n, S, counts);                  \
+    hipLaunchKernelGGL(k_mc_copy<SHF_>, dim3(copy_blocks), dim3(256), 0, s, S, dsum + nb, n_add, n, wsum + nb,  \
+                       dead, samples)
+    switch (sh_degree) {
+        case 0: LP_MC(3); break;
+        case 1: LP_MC(12); break;
+        case 2: LP_MC(27); break;
+        default: LP_MC(48); break;
+    }
+#undef LP_MC
     return hipGetLastError();
 }
 

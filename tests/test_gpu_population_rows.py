@@ -7,9 +7,10 @@ import numpy as np
 import pytest
 import torch
 
+from oracle import mcmc as MC
 from oracle import population as POP
 from paper_2501_16312_amd import linprim as L
-from paper_2501_16312_amd.population import PopulationControl
+from paper_2501_16312_amd.population import MCMC, PopulationControl
 
 pytestmark = pytest.mark.gpu
 FIELDS = ("means", "quats", "dists", "opacity", "sh")
@@ -64,3 +65,39 @@ def test_densify_rows(kind, n, degree, shift, with_moments):
     for k in FIELDS:
         assert np.array_equal(newm[k].cpu().numpy().astype(np.float64), ref_m[("m", k)]), k
         assert np.array_equal(newv[k].cpu().numpy().astype(np.float64), ref_m[("v", k)]), k
+
+
+@pytest.mark.parametrize("n,degree,shift,dead", [(1023, 0, 0, 0.3), (1024, 1, 1, 0.1), (1025, 2, 0, 0.99),
+                                                 (4100, 3, 2, 0.05), (2, 3, 0, 0.5)])
+def test_relocate_and_add_rows(n, degree, shift, dead):
+    """dead 0.99: a few sources are drawn up to the cap of 51 copies."""
+    print(f"mcmc rows n={n} degree={degree} shift={shift} dead={dead}", flush=True)
+    params, moments, _, _ = _state(L.OCTAHEDRON, n, degree, seed=n)
+    rng = np.random.default_rng(n)
+    op = rng.uniform(0.006, 0.9, size=n).astype(np.float32)
+    op[: int(dead * n)] = 0.004
+    params["opacity"] = rng.permutation(op)
+    r = rng.integers(0, 2 ** 32, size=n, dtype=np.uint64).astype(np.uint32)
+    n_add = max(1, n // 3)
+    rd = torch.as_tensor(r.view(np.int32), device="cuda")
+
+    def check(got, ref):
+        (p, m, v), (op_, om) = got, ref
+        for k in ("means", "quats", "sh"):
+            assert np.array_equal(p[k].cpu().numpy().astype(np.float64), op_[k]), k
+        for k in ("dists", "opacity"):
+            np.testing.assert_allclose(p[k].cpu().numpy(), op_[k], rtol=1e-6, err_msg=k)
+        for k in FIELDS:
+            assert np.array_equal(m[k].cpu().numpy().astype(np.float64), om[("m", k)]), k
+            assert np.array_equal(v[k].cpu().numpy().astype(np.float64), om[("v", k)]), k
+
+    P, M, V = ({k: _dev(a[k], shift) for k in FIELDS} for a in
+               (params, {k: moments[("m", k)] for k in FIELDS}, {k: moments[("v", k)] for k in FIELDS}))
+    mc = MCMC(n, degree)
+    got = mc.add(P, n_add, M, V, rand_u32=rd[:n_add].contiguous())
+    check(got, MC.add(params, moments, n_add, r[:n_add]))
+    mc = MCMC(n, degree)
+    mc.relocate(P, M, V, rand_u32=rd)
+    ref_p, ref_m, nd = MC.relocate(params, moments, r)
+    assert mc.dead_count() == nd == int((params["opacity"] <= 0.005).sum())
+    check((P, M, V), (ref_p, ref_m))
