@@ -5,55 +5,165 @@
 //   s = (2 mx my + C1)(2 sxy + C2) / ((mx^2 + my^2 + C1)(sxx + syy + C2)),
 // local statistics by an 11 x 11 Gaussian window (sigma 1.5, zero padding).
 //
-// Two passes over 32 x 32 output tiles, each staging a 42 x 42 input tile
-// (5-pixel halo) in LDS and applying the separable window as a row pass then
-// a column pass:
+// Two passes over 32 x 32 output tiles, each applying the separable window as
+// a row pass (four neighbouring outputs of a row per thread, straight from
+// global memory) and a column pass (through LDS):
 //   k_ssim_fwd  five statistics -> s and its partial derivatives with respect
 //               to mx, E[x^2], E[xy] (written per pixel), block sums of s and
 //               |x - y|;
 //   k_ssim_bwd  the window applied to those three derivative maps (the window
 //               is symmetric, so it is its own adjoint) ->
 //               dL/dx = (1 - lam) sign(x - y) / n - lam / n (G*A + 2 x G*B + y G*C).
+//
+// What bounds them, per 1080p view: the forward issues 25M VALU instructions
+// (40 us of issue) for 125 MB of traffic and takes 51 us; the backward issues
+// 12.5M (20 us) for 150 MB and takes 38 us, 3.9 TB/s (71 and 59 us when the
+// inputs were staged in LDS first, with a barrier between).  Tiles of 32 x 48
+// take as long, 32 x 64 13% longer (fewer waves per SIMD).
 #include "linprim_common.h"
 
 namespace linprim {
 
-constexpr int kSsimTile = 32;
 constexpr int kSsimHalo = 5;
-constexpr int kSsimIn = kSsimTile + 2 * kSsimHalo;   // 42
-constexpr float kC1 = 0.0001f;                       // 0.01^2
-constexpr float kC2 = 0.0009f;                       // 0.03^2
+constexpr int kRun = 4;                      // outputs of a row per thread of a row pass
+constexpr int kRuns = kLossTile / kRun;      // runs per row of a tile
+constexpr int kRowsIn = kLossTile + 2 * kSsimHalo;
+constexpr float kC1 = 0.0001f;               // 0.01^2
+constexpr float kC2 = 0.0009f;               // 0.03^2
 
 struct SsimWindow {
     float w[11];
 };
 
-// Loads 42 x 42 tiles of NT images (zero outside the image) into LDS.  All
-// of a thread's global loads are issued before the first LDS store, so the
-// block waits for memory once rather than once per element.
-constexpr int kTileElems = kSsimIn * kSsimIn;             // 1764
-constexpr int kLoadIters = (kTileElems + 255) / 256;      // 7 for 256 threads
-template <int NT>
-__device__ inline void load_tiles(const float* const (&src)[NT], int W, int H, int x0, int y0,
-                                  float* const (&dst)[NT]) {
-    float v[NT][kLoadIters];
+// The 14 inputs of the four outputs at columns x .. x + 3 of row y: columns
+// x - 5 .. x + 8 (v[3] .. v[16]), zero outside the image.  In a tile away from
+// the borders (`inner`, the same for the whole block) as five 16-byte loads from column x - 8 (x is a multiple of 4, so
+// they are aligned where the rows are; the type only promises 4 bytes).
+struct __attribute__((packed, aligned(4))) Float4u {
+    float v[4];
+};
+constexpr int kIn = kRun + 2 * kSsimHalo;    // 14
+template <bool INNER>
+__device__ inline void load_run(const float* __restrict__ img, int W, int H, int x, int y, float (&v)[20]) {
+    if (INNER) {
+        const float* row = img + (int64_t)y * W + (x - 8);
 #pragma unroll
-    for (int it = 0; it < kLoadIters; ++it) {
-        const int k = (int)threadIdx.x + it * 256;
-        const int r = k / kSsimIn, c = k - r * kSsimIn;
-        const int y = y0 - kSsimHalo + r, x = x0 - kSsimHalo + c;
-        const bool in = k < kTileElems && x >= 0 && x < W && y >= 0 && y < H;
-        const int64_t off = in ? (int64_t)y * W + x : 0;
+        for (int k = 0; k < 5; ++k) {
+            const Float4u q = *reinterpret_cast<const Float4u*>(row + 4 * k);
 #pragma unroll
-        for (int m = 0; m < NT; ++m) v[m][it] = in ? src[m][off] : 0.0f;
+            for (int j = 0; j < 4; ++j) v[4 * k + j] = q.v[j];
+        }
+        return;
     }
 #pragma unroll
-    for (int it = 0; it < kLoadIters; ++it) {
-        const int k = (int)threadIdx.x + it * 256;
-        if (k < kTileElems) {
+    for (int k = 0; k < 20; ++k) {
+        const int c = x - 8 + k;
+        const bool in = k >= 3 && k < 3 + kIn && c >= 0 && c < W && y >= 0 && y < H;
+        v[k] = in ? img[(int64_t)y * W + c] : 0.0f;
+    }
+}
+
+// Tile of block b of a launch of T tiles padded to a multiple of 8 blocks:
+// consecutive blocks go to different XCDs, so XCD x = b % 8 is given the tiles
+// x ceil(T / 8) .. , in order, whose halos then meet in its L2 (four 1080p
+// views: 342 us against 405 in plain order).
+struct SsimTile {
+    int x0, y0, ch;
+    uint32_t index;
+    bool valid, inner;   // inner: every input of the tile's row pass, in 20-column runs, is in the image
+};
+__device__ inline SsimTile ssim_tile(int W, int H) {
+    const uint32_t tx = (uint32_t)(W + kLossTile - 1) / kLossTile, ty = (uint32_t)(H + kLossTile - 1) / kLossTile;
+    const uint32_t t = (blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3);
+    const uint32_t ch = t / (tx * ty), r = t - ch * (tx * ty);
+    const uint32_t row = r / tx;
+    SsimTile T;
+    T.x0 = (int)(r - row * tx) * kLossTile;
+    T.y0 = (int)row * kLossTile;
+    T.ch = (int)ch;
+    T.index = t;
+    T.valid = ch < 3;
+    T.inner = T.x0 >= 8 && T.x0 + kLossTile + 8 <= W && T.y0 >= kSsimHalo && T.y0 + kLossTile + kSsimHalo <= H;
+    return T;
+}
+
+__device__ inline float wave_sum_f(float v) {
+    for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off, 64);
+    return v;
+}
+
+// Row pass of the forward: the five statistics of every row of the tile and
+// its halo, and the sum of |x - y| over the tile's own pixels.
+template <bool INNER>
+__device__ inline void ssim_rows(const float* __restrict__ X, const float* __restrict__ Y, int W, int H, int x0, int y0,
+                                 const SsimWindow& win, float (*hs)[kRowsIn * kLossTile], float& l1) {
+    for (int k = threadIdx.x; k < kRowsIn * kRuns; k += 256) {
+        const int r = k / kRuns, c0 = (k % kRuns) * kRun;
+        const int y = y0 - kSsimHalo + r;
+        float xv[20], yv[20];
+        load_run<INNER>(X, W, H, x0 + c0, y, xv);
+        load_run<INNER>(Y, W, H, x0 + c0, y, yv);
+        float acc[5][kRun];
 #pragma unroll
-            for (int m = 0; m < NT; ++m) dst[m][k] = v[m][it];
+        for (int q = 0; q < kRun; ++q)
+#pragma unroll
+            for (int m = 0; m < 5; ++m) acc[m][q] = 0.f;
+#pragma unroll
+        for (int i = 0; i < kIn; ++i) {
+            const float a = xv[i + 3], b = yv[i + 3];
+            const float aa = a * a, bb = b * b, ab = a * b;
+#pragma unroll
+            for (int q = 0; q < kRun; ++q) {
+                const int u = i - q;     // tap of output c0 + q
+                if (u < 0 || u > 10) continue;
+                const float wt = win.w[u];
+                acc[0][q] += wt * a;
+                acc[1][q] += wt * b;
+                acc[2][q] += wt * aa;
+                acc[3][q] += wt * bb;
+                acc[4][q] += wt * ab;
+            }
         }
+        // the tile's own pixels (zero beyond the image on both sides)
+        if (r >= kSsimHalo && r < kSsimHalo + kLossTile) {
+#pragma unroll
+            for (int q = 0; q < kRun; ++q)
+                if (INNER || x0 + c0 + q < W) l1 += fabsf(xv[8 + q] - yv[8 + q]);
+        }
+#pragma unroll
+        for (int m = 0; m < 5; ++m)
+            *reinterpret_cast<float4*>(&hs[m][r * kLossTile + c0]) = make_float4(acc[m][0], acc[m][1], acc[m][2], acc[m][3]);
+    }
+}
+
+// Row pass of the backward: the three derivative maps.
+template <bool INNER>
+__device__ inline void ssim_rows_bwd(const float* __restrict__ dm, int64_t hw, int W, int H, int x0, int y0,
+                                     const SsimWindow& win, float (*hs)[kRowsIn * kLossTile]) {
+    for (int k = threadIdx.x; k < kRowsIn * kRuns; k += 256) {
+        const int r = k / kRuns, c0 = (k % kRuns) * kRun;
+        float v[3][20];
+#pragma unroll
+        for (int m = 0; m < 3; ++m) load_run<INNER>(dm + m * hw, W, H, x0 + c0, y0 - kSsimHalo + r, v[m]);
+        float acc[3][kRun];
+#pragma unroll
+        for (int q = 0; q < kRun; ++q)
+#pragma unroll
+            for (int m = 0; m < 3; ++m) acc[m][q] = 0.f;
+#pragma unroll
+        for (int i = 0; i < kIn; ++i) {
+#pragma unroll
+            for (int q = 0; q < kRun; ++q) {
+                const int u = i - q;
+                if (u < 0 || u > 10) continue;
+                const float wt = win.w[u];
+#pragma unroll
+                for (int m = 0; m < 3; ++m) acc[m][q] += wt * v[m][i + 3];
+            }
+        }
+#pragma unroll
+        for (int m = 0; m < 3; ++m)
+            *reinterpret_cast<float4*>(&hs[m][r * kLossTile + c0]) = make_float4(acc[m][0], acc[m][1], acc[m][2], acc[m][3]);
     }
 }
 
@@ -61,69 +171,37 @@ __global__ __launch_bounds__(256) void k_ssim_fwd(const float* __restrict__ rgb,
                                                   int W, int H, SsimWindow win, float* __restrict__ dmaps,
                                                   float* __restrict__ partial, const uint32_t* __restrict__ skip) {
     if (skip && *skip) return;
-    __shared__ float xs[kSsimIn * kSsimIn], ys[kSsimIn * kSsimIn];
-    __shared__ float hs[5][kSsimIn * kSsimTile];
-    __shared__ float red[2][256];
-    const int ch = blockIdx.z;
-    const int x0 = blockIdx.x * kSsimTile, y0 = blockIdx.y * kSsimTile;
+    __shared__ __attribute__((aligned(16))) float hs[5][kRowsIn * kLossTile];
+    __shared__ float red[2][4];
+    const SsimTile tile = ssim_tile(W, H);
+    if (!tile.valid) return;
+    const int ch = tile.ch, x0 = tile.x0, y0 = tile.y0;
     const int64_t hw = (int64_t)W * H;
     const float* X = rgb + ch * hw;
     const float* Y = target + ch * hw;
-    {
-        const float* const srcs[2] = {X, Y};
-        float* const dsts[2] = {xs, ys};
-        load_tiles<2>(srcs, W, H, x0, y0, dsts);
-    }
-    __syncthreads();
-    // row pass: 42 rows x 32 output columns, five statistics; a thread
-    // takes 4 neighbouring outputs of a row and slides over 14 inputs
-    constexpr int RUN = 4, NRUN = kSsimTile / RUN;     // 8 runs per row
-    for (int k = threadIdx.x; k < kSsimIn * NRUN; k += 256) {
-        const int r = k / NRUN, c0 = (k % NRUN) * RUN;
-        float acc[5][RUN];
-#pragma unroll
-        for (int q = 0; q < RUN; ++q)
-#pragma unroll
-            for (int m = 0; m < 5; ++m) acc[m][q] = 0.f;
-#pragma unroll
-        for (int i = 0; i < RUN + 10; ++i) {
-            const float xv = xs[r * kSsimIn + c0 + i], yv = ys[r * kSsimIn + c0 + i];
-            const float xx = xv * xv, yy = yv * yv, xy = xv * yv;
-#pragma unroll
-            for (int q = 0; q < RUN; ++q) {
-                const int u = i - q;     // tap of output c0 + q
-                if (u < 0 || u > 10) continue;
-                const float wt = win.w[u];
-                acc[0][q] += wt * xv;
-                acc[1][q] += wt * yv;
-                acc[2][q] += wt * xx;
-                acc[3][q] += wt * yy;
-                acc[4][q] += wt * xy;
-            }
-        }
-#pragma unroll
-        for (int q = 0; q < RUN; ++q)
-#pragma unroll
-            for (int m = 0; m < 5; ++m) hs[m][r * kSsimTile + c0 + q] = acc[m][q];
-    }
+    float ssum = 0.f, l1 = 0.f;
+    if (tile.inner)
+        ssim_rows<true>(X, Y, W, H, x0, y0, win, hs, l1);
+    else
+        ssim_rows<false>(X, Y, W, H, x0, y0, win, hs, l1);
     __syncthreads();
     // column pass: a thread takes 4 neighbouring rows of one column
     // (lanes run along a row, so the map stores are coalesced)
-    float ssum = 0.f, l1 = 0.f;
     {
-        const int c = threadIdx.x % kSsimTile, r0 = (threadIdx.x / kSsimTile) * RUN;   // 8 x 4 rows
-        float acc[5][RUN];
+        constexpr int PER = kLossTile / 8;
+        const int c = threadIdx.x % kLossTile, r0 = (threadIdx.x / kLossTile) * PER;
+        float acc[5][PER];
 #pragma unroll
-        for (int q = 0; q < RUN; ++q)
+        for (int q = 0; q < PER; ++q)
 #pragma unroll
             for (int m = 0; m < 5; ++m) acc[m][q] = 0.f;
 #pragma unroll
-        for (int i = 0; i < RUN + 10; ++i) {
+        for (int i = 0; i < PER + 10; ++i) {
             float v[5];
 #pragma unroll
-            for (int m = 0; m < 5; ++m) v[m] = hs[m][(r0 + i) * kSsimTile + c];
+            for (int m = 0; m < 5; ++m) v[m] = hs[m][(r0 + i) * kLossTile + c];
 #pragma unroll
-            for (int q = 0; q < RUN; ++q) {
+            for (int q = 0; q < PER; ++q) {
                 const int u = i - q;
                 if (u < 0 || u > 10) continue;
                 const float wt = win.w[u];
@@ -132,10 +210,10 @@ __global__ __launch_bounds__(256) void k_ssim_fwd(const float* __restrict__ rgb,
             }
         }
         float* dm = dmaps + (int64_t)ch * 3 * hw;
+        const int x = x0 + c;
 #pragma unroll
-        for (int q = 0; q < RUN; ++q) {
-            const int r = r0 + q;
-            const int x = x0 + c, y = y0 + r;
+        for (int q = 0; q < PER; ++q) {
+            const int y = y0 + r0 + q;
             if (x >= W || y >= H) continue;
             const float mx = acc[0][q], my = acc[1][q], exx = acc[2][q], eyy = acc[3][q], exy = acc[4][q];
             const float A = 2.f * mx * my + kC1;
@@ -149,24 +227,19 @@ __global__ __launch_bounds__(256) void k_ssim_fwd(const float* __restrict__ rgb,
             dm[hw + p] = -sv / D;                                                       // ds/dE[x^2]
             dm[2 * hw + p] = 2.f * A * icd;                                            // ds/dE[xy]
             ssum += sv;
-            l1 += fabsf(xs[(r + kSsimHalo) * kSsimIn + c + kSsimHalo] - ys[(r + kSsimHalo) * kSsimIn + c + kSsimHalo]);
         }
     }
     // block sums, fixed order
-    red[0][threadIdx.x] = ssum;
-    red[1][threadIdx.x] = l1;
-    __syncthreads();
-    for (int off = 128; off > 0; off >>= 1) {
-        if ((int)threadIdx.x < off) {
-            red[0][threadIdx.x] += red[0][threadIdx.x + off];
-            red[1][threadIdx.x] += red[1][threadIdx.x + off];
-        }
-        __syncthreads();
+    ssum = wave_sum_f(ssum);
+    l1 = wave_sum_f(l1);
+    if ((threadIdx.x & 63) == 0) {
+        red[0][threadIdx.x >> 6] = ssum;
+        red[1][threadIdx.x >> 6] = l1;
     }
-    if (threadIdx.x == 0) {
-        const int64_t b = ((int64_t)ch * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x;
-        partial[2 * b] = red[0][0];
-        partial[2 * b + 1] = red[1][0];
+    __syncthreads();
+    if (threadIdx.x < 2) {
+        const float* q = red[threadIdx.x];
+        partial[2 * tile.index + threadIdx.x] = (q[0] + q[1]) + (q[2] + q[3]);
     }
 }
 
@@ -175,64 +248,46 @@ __global__ __launch_bounds__(256) void k_ssim_bwd(const float* __restrict__ rgb,
                                                   float l1_scale, float ssim_scale, float* __restrict__ grad,
                                                   const uint32_t* __restrict__ skip) {
     if (skip && *skip) return;
-    __shared__ float ts[3][kSsimIn * kSsimIn];
-    __shared__ float hs[3][kSsimIn * kSsimTile];
-    const int ch = blockIdx.z;
-    const int x0 = blockIdx.x * kSsimTile, y0 = blockIdx.y * kSsimTile;
+    __shared__ __attribute__((aligned(16))) float hs[3][kRowsIn * kLossTile];
+    const SsimTile tile = ssim_tile(W, H);
+    if (!tile.valid) return;
+    const int ch = tile.ch, x0 = tile.x0, y0 = tile.y0;
     const int64_t hw = (int64_t)W * H;
     const float* dm = dmaps + (int64_t)ch * 3 * hw;
-    {
-        const float* const srcs[3] = {dm, dm + hw, dm + 2 * hw};
-        float* const dsts[3] = {ts[0], ts[1], ts[2]};
-        load_tiles<3>(srcs, W, H, x0, y0, dsts);
-    }
-    __syncthreads();
-    // row pass over the three maps, 4 outputs per thread (sliding window)
-    constexpr int RUN = 4, NRUN = kSsimTile / RUN;
-    for (int k = threadIdx.x; k < kSsimIn * NRUN; k += 256) {
-        const int r = k / NRUN, c0 = (k % NRUN) * RUN;
-        float acc[3][RUN];
-#pragma unroll
-        for (int q = 0; q < RUN; ++q)
-#pragma unroll
-            for (int m = 0; m < 3; ++m) acc[m][q] = 0.f;
-#pragma unroll
-        for (int i = 0; i < RUN + 10; ++i) {
-            float v[3];
-#pragma unroll
-            for (int m = 0; m < 3; ++m) v[m] = ts[m][r * kSsimIn + c0 + i];
-#pragma unroll
-            for (int q = 0; q < RUN; ++q) {
-                const int u = i - q;
-                if (u < 0 || u > 10) continue;
-                const float wt = win.w[u];
-#pragma unroll
-                for (int m = 0; m < 3; ++m) acc[m][q] += wt * v[m];
-            }
-        }
-#pragma unroll
-        for (int q = 0; q < RUN; ++q)
-#pragma unroll
-            for (int m = 0; m < 3; ++m) hs[m][r * kSsimTile + c0 + q] = acc[m][q];
-    }
-    __syncthreads();
+    if (tile.inner)
+        ssim_rows_bwd<true>(dm, hw, W, H, x0, y0, win, hs);
+    else
+        ssim_rows_bwd<false>(dm, hw, W, H, x0, y0, win, hs);
     const float* X = rgb + ch * hw;
     const float* Y = target + ch * hw;
     float* G = grad + ch * hw;
-    // column pass: 4 neighbouring rows of one column per thread
-    const int c = threadIdx.x % kSsimTile, r0 = (threadIdx.x / kSsimTile) * RUN;
-    float acc[3][RUN];
+    // column pass: 4 neighbouring rows of one column per thread, the
+    // image's own pixels loaded before the barrier
+    constexpr int PER = kLossTile / 8;
+    const int c = threadIdx.x % kLossTile, r0 = (threadIdx.x / kLossTile) * PER;
+    const int x = x0 + c;
+    float px[PER], py[PER];
 #pragma unroll
-    for (int q = 0; q < RUN; ++q)
+    for (int q = 0; q < PER; ++q) {
+        const int y = y0 + r0 + q;
+        const bool in = x < W && y < H;
+        const int64_t p = (int64_t)y * W + x;
+        px[q] = in ? X[p] : 0.0f;
+        py[q] = in ? Y[p] : 0.0f;
+    }
+    __syncthreads();
+    float acc[3][PER];
+#pragma unroll
+    for (int q = 0; q < PER; ++q)
 #pragma unroll
         for (int m = 0; m < 3; ++m) acc[m][q] = 0.f;
 #pragma unroll
-    for (int i = 0; i < RUN + 10; ++i) {
+    for (int i = 0; i < PER + 10; ++i) {
         float v[3];
 #pragma unroll
-        for (int m = 0; m < 3; ++m) v[m] = hs[m][(r0 + i) * kSsimTile + c];
+        for (int m = 0; m < 3; ++m) v[m] = hs[m][(r0 + i) * kLossTile + c];
 #pragma unroll
-        for (int q = 0; q < RUN; ++q) {
+        for (int q = 0; q < PER; ++q) {
             const int u = i - q;
             if (u < 0 || u > 10) continue;
             const float wt = win.w[u];
@@ -241,14 +296,13 @@ __global__ __launch_bounds__(256) void k_ssim_bwd(const float* __restrict__ rgb,
         }
     }
 #pragma unroll
-    for (int q = 0; q < RUN; ++q) {
-        const int x = x0 + c, y = y0 + r0 + q;
+    for (int q = 0; q < PER; ++q) {
+        const int y = y0 + r0 + q;
         if (x >= W || y >= H) continue;
-        const int64_t p = (int64_t)y * W + x;
-        const float xv = X[p], yv = Y[p];
+        const float xv = px[q], yv = py[q];
         const float d = xv - yv;
         const float sg = d > 0.f ? 1.f : (d < 0.f ? -1.f : 0.f);
-        G[p] = l1_scale * sg - ssim_scale * (acc[0][q] + 2.f * xv * acc[1][q] + yv * acc[2][q]);
+        G[(int64_t)y * W + x] = l1_scale * sg - ssim_scale * (acc[0][q] + 2.f * xv * acc[1][q] + yv * acc[2][q]);
     }
 }
 
@@ -268,9 +322,10 @@ SsimWindow ssim_window() {
 hipError_t launch_ssim_l1(const float* rgb, const float* target, int W, int H, float lam, float* dmaps,
                           float* partial, float* grad, const uint32_t* skip, hipStream_t s) {
     const SsimWindow win = ssim_window();
-    const dim3 grid((unsigned)((W + kSsimTile - 1) / kSsimTile), (unsigned)((H + kSsimTile - 1) / kSsimTile), 3);
-    hipLaunchKernelGGL(k_ssim_fwd, grid, dim3(256), 0, s, rgb, target, W, H, win, dmaps, partial, skip);
+    const int64_t tiles = (int64_t)((W + kLossTile - 1) / kLossTile) * ((H + kLossTile - 1) / kLossTile) * 3;
+    const dim3 grid((unsigned)((tiles + 7) & ~int64_t(7)));
     const float n = 3.0f * (float)W * (float)H;
+    hipLaunchKernelGGL(k_ssim_fwd, grid, dim3(256), 0, s, rgb, target, W, H, win, dmaps, partial, skip);
     hipLaunchKernelGGL(k_ssim_bwd, grid, dim3(256), 0, s, rgb, target, W, H, win, dmaps, (1.0f - lam) / n, lam / n,
                        grad, skip);
     return hipGetLastError();
