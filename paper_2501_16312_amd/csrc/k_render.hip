@@ -120,6 +120,36 @@ __device__ inline void load_rec(const float* __restrict__ rec, Rec& R) {
     R.fmap = (EXACT || KIND == LINPRIM_OCTAHEDRON) ? 0 : __float_as_int(rec[R_FACEMAP]);
 }
 
+// The record words 4.. of an entry staged in LDS, as 16-byte quads.
+template <int KIND, bool EXACT>
+constexpr int rec_quads() {
+    return (EXACT || KIND == LINPRIM_OCTAHEDRON) ? 6 : 7;
+}
+template <int KIND, bool EXACT>
+__device__ inline void load_rec_lds(const float4* q, Rec& R) {
+    constexpr int NQD = rec_quads<KIND, EXACT>();
+    float w[4 * NQD];
+#pragma unroll
+    for (int k = 0; k < NQD; ++k) {
+        const float4 v = q[k];
+        w[4 * k] = v.x;
+        w[4 * k + 1] = v.y;
+        w[4 * k + 2] = v.z;
+        w[4 * k + 3] = v.w;
+    }
+    R.s2 = w[0];
+    R.r = w[1];
+    R.g = w[2];
+    R.b = w[3];
+    R.fi0 = w[4];
+    R.fj0 = w[5];
+    R.fwi = w[6];
+    R.fwj = w[7];
+    constexpr int NP = (EXACT || KIND == LINPRIM_OCTAHEDRON) ? 16 : 18;
+#pragma unroll
+    for (int k = 0; k < NP; ++k) R.p[k] = w[8 + k];
+}
+
 // Returns hi - lo; ih / il are the active upper / lower slot (first on ties).
 template <int KIND>
 __device__ inline float chord(const Rec& R, float ki, float kj, int& ih, int& il) {
@@ -364,6 +394,17 @@ __device__ inline Batch load_batch(const float* __restrict__ base, const uint32_
 // parameter tau); the centre's depth is added once per pixel afterwards.
 constexpr float kDepthT = 0.5f;
 
+// Long lists set the kernel's end: a wave issues one instruction every four
+// cycles at best, and the scalar walk's bookkeeping, waits for scalar loads
+// and 42 VALU instructions came to 300 ns an entry under full load (170 ns
+// alone).  Lists of more than kStagedList pairs are walked with their records
+// staged in LDS, 32 entries at a time, the next 32 on their way in registers,
+// at a raised wave priority (1M octahedra at 1080p, longest list 499: kernel
+// 126 -> 90 us).  Shorter lists have the chip's other waves to hide behind, and
+// take fewer registers and issue slots with scalar loads (from 64, 96 or 256
+// pairs on: the same within 2 us, and 52 -> 57 us at 64 with 16-pixel tiles).
+constexpr uint32_t kStagedList = 128;
+
 __device__ inline double centre_depth(const ViewInfo& V, const float* __restrict__ means, uint32_t prim, bool exact) {
     const double x = means[3 * (size_t)prim], y = means[3 * (size_t)prim + 1], z = means[3 * (size_t)prim + 2];
     const double t0 = V.Rw[0] * x + V.Rw[1] * y + V.Rw[2] * z + V.tw[0];
@@ -373,7 +414,7 @@ __device__ inline double centre_depth(const ViewInfo& V, const float* __restrict
 }
 
 template <int TILE, int KIND, bool COUNT, bool EXACT, bool DEPTH>
-__global__ __launch_bounds__(64) void k_render_fwd(const ViewInfo* __restrict__ views, int n_views, int64_t n,
+__global__ __launch_bounds__(64, 6) void k_render_fwd(const ViewInfo* __restrict__ views, int n_views, int64_t n,
                                                    const float* __restrict__ payload, const uint32_t* __restrict__ vals,
                                                    const uint2* __restrict__ ranges, const Status* __restrict__ status,
                                                    uint64_t capacity, float bg0, float bg1, float bg2,
@@ -382,6 +423,8 @@ __global__ __launch_bounds__(64) void k_render_fwd(const ViewInfo* __restrict__ 
                                                    unsigned long long* __restrict__ counters,
                                                    const float* __restrict__ means,
                                                    float* __restrict__ out_depth, const uint32_t* __restrict__ order) {
+    __shared__ float4 srec[36][rec_quads<KIND, EXACT>()];
+    __shared__ uint32_t spos[32];
     if (status->n_pairs > capacity) return;
     constexpr int QX = TILE / 8, NQ = QX * QX;
     const Place P = place_wave<TILE>(views, n_views, order);
@@ -403,85 +446,146 @@ __global__ __launch_bounds__(64) void k_render_fwd(const ViewInfo* __restrict__ 
     const float* base = payload + (size_t)P.v * (size_t)n * kRecordWords;
     bool alive = true;
     uint32_t sink = 0;   // keeps the L2-warming loads alive; never stored
-    Batch nxt = load_batch<NQ, false>(base, vals, nullptr, rg.x, min(64u, rg.y - rg.x), P.gx0, P.gy0);
-    for (uint32_t e0 = rg.x; e0 < rg.y && alive; e0 += 64) {
-        Batch cur = nxt;
-        const uint32_t e1 = e0 + 64;
-        if (e1 < rg.y) nxt = load_batch<NQ, false>(base, vals, nullptr, e1, min(64u, rg.y - e1), P.gx0, P.gy0);
-        sink ^= cur.touch;
-        uint64_t mask = cur.mask;
-        if (!mask) continue;
-        // Two record buffers used in turn: the next surviving entry's record
-        // is loaded into one while the other is blended, with no copies.
-        auto blend = [&](const Rec& R, uint32_t e) {
-            // Branch-free: lanes that do not see the primitive blend with
-            // 1 - o = 1 exactly, which leaves C and T unchanged.
-            const float ki = pxf - R.fi0, kj = pyf - R.fj0;
-            // bitwise &: every test is a plain compare, no short-circuit branches
-            // lane masks of single compares combine in scalar registers
-            const uint64_t m_in = __builtin_amdgcn_ballot_w64(fabsf(ki) <= R.fwi) &
-                                  __builtin_amdgcn_ballot_w64(fabsf(kj) <= R.fwj) & live;
-            const bool inside = __builtin_amdgcn_inverse_ballot_w64(m_in);
-            float dch, entry = 0.0f;
-            if (EXACT) {
-                ExactPlanes X;
-                exact_planes<KIND>(R, ki, kj, X);
-                dch = exact_chord(X, rn);
-                entry = X.L;
-            } else if (DEPTH) {
-                dch = chord_entry<KIND>(R, ki, kj, entry);
-            } else {
-                dch = chord_fast<KIND>(R, ki, kj);
-            }
-            const uint64_t m_hit = m_in & __builtin_amdgcn_ballot_w64(dch > 0.0f);
-            const bool hitp = __builtin_amdgcn_inverse_ballot_w64(m_hit);
-            if (COUNT) {
-                ev += inside ? 1u : 0u;
-                hit += hitp ? 1u : 0u;
-            }
-            const float ex = hitp ? chord_exp(R.s2, dch) : 1.0f;
-            const float onemo = fmaxf(ex, kOneMinusOMax);
-            const float w = T * (1.0f - onemo);
-            C0 = __builtin_fmaf(w, R.r, C0);
-            C1 = __builtin_fmaf(w, R.g, C1);
-            C2 = __builtin_fmaf(w, R.b, C2);
-            if (DEPTH) {
-                const bool cross = T >= kDepthT && T * onemo < kDepthT;
-                half = cross ? e : half;
-                half_entry = cross ? entry : half_entry;
-            }
-            T = T * onemo;
-            last = hitp ? (int)e + 1 : last;
-            // T only falls where the primitive was hit
-            const uint64_t stop = __builtin_amdgcn_ballot_w64(T <= kTStop) & m_hit;
-            if (COUNT) term = __builtin_amdgcn_inverse_ballot_w64(stop) ? e + 1 : term;
-            live &= ~stop;
-            return live != 0;
+    auto blend = [&](const Rec& R, uint32_t e) {
+        // Branch-free: lanes that do not see the primitive blend with
+        // 1 - o = 1 exactly, which leaves C and T unchanged.
+        const float ki = pxf - R.fi0, kj = pyf - R.fj0;
+        // bitwise &: every test is a plain compare, no short-circuit branches
+        // lane masks of single compares combine in scalar registers
+        const uint64_t m_in = __builtin_amdgcn_ballot_w64(fabsf(ki) <= R.fwi) &
+                              __builtin_amdgcn_ballot_w64(fabsf(kj) <= R.fwj) & live;
+        const bool inside = __builtin_amdgcn_inverse_ballot_w64(m_in);
+        float dch, entry = 0.0f;
+        if (EXACT) {
+            ExactPlanes X;
+            exact_planes<KIND>(R, ki, kj, X);
+            dch = exact_chord(X, rn);
+            entry = X.L;
+        } else if (DEPTH) {
+            dch = chord_entry<KIND>(R, ki, kj, entry);
+        } else {
+            dch = chord_fast<KIND>(R, ki, kj);
+        }
+        const uint64_t m_hit = m_in & __builtin_amdgcn_ballot_w64(dch > 0.0f);
+        const bool hitp = __builtin_amdgcn_inverse_ballot_w64(m_hit);
+        if (COUNT) {
+            ev += inside ? 1u : 0u;
+            hit += hitp ? 1u : 0u;
+        }
+        const float ex = hitp ? chord_exp(R.s2, dch) : 1.0f;
+        const float onemo = fmaxf(ex, kOneMinusOMax);
+        const float w = T * (1.0f - onemo);
+        C0 = __builtin_fmaf(w, R.r, C0);
+        C1 = __builtin_fmaf(w, R.g, C1);
+        C2 = __builtin_fmaf(w, R.b, C2);
+        if (DEPTH) {
+            const bool cross = T >= kDepthT && T * onemo < kDepthT;
+            half = cross ? e : half;
+            half_entry = cross ? entry : half_entry;
+        }
+        T = T * onemo;
+        last = hitp ? (int)e + 1 : last;
+        // T only falls where the primitive was hit
+        const uint64_t stop = __builtin_amdgcn_ballot_w64(T <= kTStop) & m_hit;
+        if (COUNT) term = __builtin_amdgcn_inverse_ballot_w64(stop) ? e + 1 : term;
+        live &= ~stop;
+        return live != 0;
+    };
+    if (rg.y - rg.x > kStagedList) {
+        constexpr int NQD = rec_quads<KIND, EXACT>(), NH = (NQD + 1) / 2;
+        __builtin_amdgcn_s_setprio(3);
+        const uint32_t sl = (uint32_t)lane & 31u, q0 = ((uint32_t)lane >> 5) * NH;
+        auto left = [&](uint32_t e) { return e < rg.y ? min(32u, rg.y - e) : 0u; };
+        auto index_at = [&](uint32_t e) { return sl < left(e) ? vals[e + sl] : 0u; };
+        // lanes l and l + 32 bring the two halves of entry l's record
+        float4 st[NH];
+        int4 rect1 = make_int4(0, 0, 0, 0);
+        auto fetch = [&](uint32_t idx) {
+            const float4* rp = reinterpret_cast<const float4*>(base + (size_t)idx * kRecordWords);
+#pragma unroll
+            for (int k = 0; k < NH; ++k) st[k] = rp[1 + min((int)q0 + k, NQD - 1)];
+            if (NQ > 1) rect1 = *reinterpret_cast<const int4*>(rp);
         };
-        auto next_rec = [&](Rec& R) {
-            const int b = __builtin_ctzll(mask);
-            mask &= mask - 1;
-            load_rec<KIND, EXACT>(base + (size_t)(uint32_t)__builtin_amdgcn_readlane((int)cur.idx, b) * kRecordWords, R);
-            return e0 + (uint32_t)b;
-        };
-        // Scalar loads complete out of order, so waiting for one buffer means
-        // waiting for every scalar load in flight: wait first, then issue
-        // the next record's load, then blend from the buffer just waited for.
-        Rec RA, RB;
-        uint32_t eA = next_rec(RA), eB = 0;
-        while (true) {
-            smem_wait_all();
-            const bool haveB = mask != 0;
-            if (haveB) eB = next_rec(RB);
-            sched_fence();
-            if (!blend(RA, eA)) { alive = false; break; }
-            if (!haveB) break;
-            smem_wait_all();
-            const bool haveA = mask != 0;
-            if (haveA) eA = next_rec(RA);
-            sched_fence();
-            if (!blend(RB, eB)) { alive = false; break; }
-            if (!haveA) break;
+        fetch(index_at(rg.x));
+        uint32_t idx1 = index_at(rg.x + 32);
+        for (uint32_t e0 = rg.x; e0 < rg.y && live; e0 += 32) {
+            // the entries that meet the group, one after the other
+            uint32_t mask = left(e0) < 32u ? (1u << left(e0)) - 1u : ~0u;
+            if (NQ > 1) mask &= (uint32_t)__ballot(rect_meets_group(rect1, P.gx0, P.gy0));
+            const int cnt = __builtin_popcount(mask);
+            if ((mask >> sl) & 1u) {
+                const int r = __builtin_popcount(mask & ((1u << sl) - 1u));
+#pragma unroll
+                for (int k = 0; k < NH; ++k)
+                    if ((int)q0 + k < NQD) srec[r][q0 + k] = st[k];
+                if (lane < 32) spos[r] = e0 + sl + 1;
+            }
+            // an odd count is filled up with a record no pixel lies in
+            if (lane < NQD) srec[cnt][lane] = (lane == 1) ? make_float4(0.f, 0.f, -1.f, -1.f) : make_float4(0.f, 0.f, 0.f, 0.f);
+            __builtin_amdgcn_wave_barrier();   // other lanes read what this one staged
+            fetch(idx1);
+            idx1 = index_at(e0 + 64);
+            // inside the batch entries count from 0; their list positions follow after it
+            const int last0 = last;
+            const uint32_t half0 = half, term0 = term;
+            last = 0;
+            half = 0xffffffffu;
+            term = 0;
+            Rec RA, RB;
+            load_rec_lds<KIND, EXACT>(srec[0], RA);
+            load_rec_lds<KIND, EXACT>(srec[1], RB);
+            for (int j = 0; j < cnt && live; j += 2) {
+                // the fences keep each record's loads a whole blend ahead of their use
+                blend(RA, (uint32_t)j);
+                sched_fence();
+                load_rec_lds<KIND, EXACT>(srec[j + 2], RA);
+                sched_fence();
+                blend(RB, (uint32_t)j + 1);
+                sched_fence();
+                load_rec_lds<KIND, EXACT>(srec[j + 3], RB);
+                sched_fence();
+            }
+            last = last ? (int)spos[last - 1] : last0;
+            if (DEPTH) half = (half != 0xffffffffu) ? spos[half] - 1 : half0;
+            if (COUNT) term = term ? spos[term - 1] : term0;
+        }
+        __builtin_amdgcn_s_setprio(0);
+    } else {
+        Batch nxt = load_batch<NQ, false>(base, vals, nullptr, rg.x, min(64u, rg.y - rg.x), P.gx0, P.gy0);
+        for (uint32_t e0 = rg.x; e0 < rg.y && alive; e0 += 64) {
+            Batch cur = nxt;
+            const uint32_t e1 = e0 + 64;
+            if (e1 < rg.y) nxt = load_batch<NQ, false>(base, vals, nullptr, e1, min(64u, rg.y - e1), P.gx0, P.gy0);
+            sink ^= cur.touch;
+            uint64_t mask = cur.mask;
+            if (!mask) continue;
+            // Two record buffers used in turn: the next surviving entry's record
+            // is loaded into one while the other is blended, with no copies.
+            auto next_rec = [&](Rec& R) {
+                const int b = __builtin_ctzll(mask);
+                mask &= mask - 1;
+                load_rec<KIND, EXACT>(base + (size_t)(uint32_t)__builtin_amdgcn_readlane((int)cur.idx, b) * kRecordWords, R);
+                return e0 + (uint32_t)b;
+            };
+            // Scalar loads complete out of order, so waiting for one buffer means
+            // waiting for every scalar load in flight: wait first, then issue
+            // the next record's load, then blend from the buffer just waited for.
+            Rec RA, RB;
+            uint32_t eA = next_rec(RA), eB = 0;
+            while (true) {
+                smem_wait_all();
+                const bool haveB = mask != 0;
+                if (haveB) eB = next_rec(RB);
+                sched_fence();
+                if (!blend(RA, eA)) { alive = false; break; }
+                if (!haveB) break;
+                smem_wait_all();
+                const bool haveA = mask != 0;
+                if (haveA) eA = next_rec(RA);
+                sched_fence();
+                if (!blend(RB, eB)) { alive = false; break; }
+                if (!haveA) break;
+            }
         }
     }
     if (n < 0) out_T[0] = __uint_as_float(sink);   // n >= 0: never taken
