@@ -16,10 +16,10 @@
 //               dL/dx = (1 - lam) sign(x - y) / n - lam / n (G*A + 2 x G*B + y G*C).
 //
 // What bounds them, per 1080p view: the forward issues 25M VALU instructions
-// (40 us of issue) for 125 MB of traffic and takes 51 us; the backward issues
-// 12.5M (20 us) for 150 MB and takes 38 us, 3.9 TB/s (71 and 59 us when the
-// inputs were staged in LDS first, with a barrier between).  Tiles of 32 x 48
-// take as long, 32 x 64 13% longer (fewer waves per SIMD).
+// (40 us of issue) for 125 MB of traffic, the backward 12.5M (20 us) for 150
+// MB; together they take 79 us (119 when the inputs were staged in LDS first,
+// with a barrier between).  Taller tiles: 32 x 48 as long, 32 x 64 13% longer
+// (fewer waves per SIMD).
 #include "linprim_common.h"
 
 namespace linprim {
@@ -55,12 +55,42 @@ __device__ inline void load_run(const float* __restrict__ img, int W, int H, int
         }
         return;
     }
+    // the same five loads, moved inside the image where they would leave it:
+    // a quad of columns is then in the image, beyond it, or, at the right
+    // border of a width that is no multiple of 4, short of its last d columns
+    const bool row_in = y >= 0 && y < H;
+    const float* row = img + (int64_t)min(max(y, 0), H - 1) * W;
+    if (W >= 4) {
 #pragma unroll
-    for (int k = 0; k < 20; ++k) {
-        const int c = x - 8 + k;
-        const bool in = k >= 3 && k < 3 + kIn && c >= 0 && c < W && y >= 0 && y < H;
-        v[k] = in ? img[(int64_t)y * W + c] : 0.0f;
+        for (int k = 0; k < 5; ++k) {
+            const int c = x - 8 + 4 * k, at = min(max(c, 0), W - 4), d = c - at;
+            const Float4u q = *reinterpret_cast<const Float4u*>(row + at);
+            const bool whole = row_in && d == 0;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) v[4 * k + j] = whole ? q.v[j] : 0.0f;
+            if (row_in && d > 0 && d < 4) {
+#pragma unroll
+                for (int j = 0; j < 3; ++j)
+                    if (c + j < W) v[4 * k + j] = row[c + j];
+            }
+        }
+    } else {
+#pragma unroll
+        for (int k = 0; k < 20; ++k) {
+            const int c = x - 8 + k;
+            v[k] = row_in && c >= 0 && c < W ? row[c] : 0.0f;
+        }
     }
+}
+
+// Different code at the end of the two forms of a row pass, so that the
+// compiler does not merge their arithmetic behind the two ways of loading:
+// merged, every run waits for all of its loads before the first product (four
+// views of 288 x 229: 42 us apart, 46 merged).
+template <bool INNER>
+__device__ inline void keep_apart() {
+    if (INNER) asm volatile("; inner tile");
+    else asm volatile("; border tile");
 }
 
 // Tile of block b of a launch of T tiles padded to a multiple of 8 blocks:
@@ -94,10 +124,10 @@ __device__ inline float wave_sum_f(float v) {
 
 // Row pass of the forward: the five statistics of every row of the tile and
 // its halo, and the sum of |x - y| over the tile's own pixels.
-template <bool INNER>
+template <int NT, bool INNER>
 __device__ inline void ssim_rows(const float* __restrict__ X, const float* __restrict__ Y, int W, int H, int x0, int y0,
                                  const SsimWindow& win, float (*hs)[kRowsIn * kLossTile], float& l1) {
-    for (int k = threadIdx.x; k < kRowsIn * kRuns; k += 256) {
+    for (int k = threadIdx.x; k < kRowsIn * kRuns; k += NT) {
         const int r = k / kRuns, c0 = (k % kRuns) * kRun;
         const int y = y0 - kSsimHalo + r;
         float xv[20], yv[20];
@@ -133,14 +163,15 @@ __device__ inline void ssim_rows(const float* __restrict__ X, const float* __res
 #pragma unroll
         for (int m = 0; m < 5; ++m)
             *reinterpret_cast<float4*>(&hs[m][r * kLossTile + c0]) = make_float4(acc[m][0], acc[m][1], acc[m][2], acc[m][3]);
+        keep_apart<INNER>();
     }
 }
 
 // Row pass of the backward: the three derivative maps.
-template <bool INNER>
+template <int NT, bool INNER>
 __device__ inline void ssim_rows_bwd(const float* __restrict__ dm, int64_t hw, int W, int H, int x0, int y0,
                                      const SsimWindow& win, float (*hs)[kRowsIn * kLossTile]) {
-    for (int k = threadIdx.x; k < kRowsIn * kRuns; k += 256) {
+    for (int k = threadIdx.x; k < kRowsIn * kRuns; k += NT) {
         const int r = k / kRuns, c0 = (k % kRuns) * kRun;
         float v[3][20];
 #pragma unroll
@@ -164,15 +195,17 @@ __device__ inline void ssim_rows_bwd(const float* __restrict__ dm, int64_t hw, i
 #pragma unroll
         for (int m = 0; m < 3; ++m)
             *reinterpret_cast<float4*>(&hs[m][r * kLossTile + c0]) = make_float4(acc[m][0], acc[m][1], acc[m][2], acc[m][3]);
+        keep_apart<INNER>();
     }
 }
 
-__global__ __launch_bounds__(256) void k_ssim_fwd(const float* __restrict__ rgb, const float* __restrict__ target,
+template <int NT>
+__global__ __launch_bounds__(NT) void k_ssim_fwd(const float* __restrict__ rgb, const float* __restrict__ target,
                                                   int W, int H, SsimWindow win, float* __restrict__ dmaps,
                                                   float* __restrict__ partial, const uint32_t* __restrict__ skip) {
     if (skip && *skip) return;
     __shared__ __attribute__((aligned(16))) float hs[5][kRowsIn * kLossTile];
-    __shared__ float red[2][4];
+    __shared__ float red[2][NT / 64];
     const SsimTile tile = ssim_tile(W, H);
     if (!tile.valid) return;
     const int ch = tile.ch, x0 = tile.x0, y0 = tile.y0;
@@ -181,14 +214,14 @@ __global__ __launch_bounds__(256) void k_ssim_fwd(const float* __restrict__ rgb,
     const float* Y = target + ch * hw;
     float ssum = 0.f, l1 = 0.f;
     if (tile.inner)
-        ssim_rows<true>(X, Y, W, H, x0, y0, win, hs, l1);
+        ssim_rows<NT, true>(X, Y, W, H, x0, y0, win, hs, l1);
     else
-        ssim_rows<false>(X, Y, W, H, x0, y0, win, hs, l1);
+        ssim_rows<NT, false>(X, Y, W, H, x0, y0, win, hs, l1);
     __syncthreads();
     // column pass: a thread takes 4 neighbouring rows of one column
     // (lanes run along a row, so the map stores are coalesced)
     {
-        constexpr int PER = kLossTile / 8;
+        constexpr int PER = kLossTile * kLossTile / NT;
         const int c = threadIdx.x % kLossTile, r0 = (threadIdx.x / kLossTile) * PER;
         float acc[5][PER];
 #pragma unroll
@@ -239,11 +272,15 @@ __global__ __launch_bounds__(256) void k_ssim_fwd(const float* __restrict__ rgb,
     __syncthreads();
     if (threadIdx.x < 2) {
         const float* q = red[threadIdx.x];
-        partial[2 * tile.index + threadIdx.x] = (q[0] + q[1]) + (q[2] + q[3]);
+        float t = 0.0f;
+#pragma unroll
+        for (int w = 0; w < NT / 64; ++w) t += q[w];
+        partial[2 * tile.index + threadIdx.x] = t;
     }
 }
 
-__global__ __launch_bounds__(256) void k_ssim_bwd(const float* __restrict__ rgb, const float* __restrict__ target,
+template <int NT>
+__global__ __launch_bounds__(NT) void k_ssim_bwd(const float* __restrict__ rgb, const float* __restrict__ target,
                                                   int W, int H, SsimWindow win, const float* __restrict__ dmaps,
                                                   float l1_scale, float ssim_scale, float* __restrict__ grad,
                                                   const uint32_t* __restrict__ skip) {
@@ -255,15 +292,15 @@ __global__ __launch_bounds__(256) void k_ssim_bwd(const float* __restrict__ rgb,
     const int64_t hw = (int64_t)W * H;
     const float* dm = dmaps + (int64_t)ch * 3 * hw;
     if (tile.inner)
-        ssim_rows_bwd<true>(dm, hw, W, H, x0, y0, win, hs);
+        ssim_rows_bwd<NT, true>(dm, hw, W, H, x0, y0, win, hs);
     else
-        ssim_rows_bwd<false>(dm, hw, W, H, x0, y0, win, hs);
+        ssim_rows_bwd<NT, false>(dm, hw, W, H, x0, y0, win, hs);
     const float* X = rgb + ch * hw;
     const float* Y = target + ch * hw;
     float* G = grad + ch * hw;
     // column pass: 4 neighbouring rows of one column per thread, the
     // image's own pixels loaded before the barrier
-    constexpr int PER = kLossTile / 8;
+    constexpr int PER = kLossTile * kLossTile / NT;
     const int c = threadIdx.x % kLossTile, r0 = (threadIdx.x / kLossTile) * PER;
     const int x = x0 + c;
     float px[PER], py[PER];
@@ -318,6 +355,11 @@ SsimWindow ssim_window() {
     return S;
 }
 
+// Up to two tiles per CU, a tile takes eight waves instead of four: the row
+// pass is one round instead of two, and nothing else waits for the waves (four
+// views of 288 x 229: 46 us against 52; at 1000 x 600, 3192 tiles, 74 against 67).
+constexpr int64_t kSsimFewTiles = 512;
+
 // One view [3, H, W]: dmaps [3][3][H][W] scratch, partial [2 * 3 * tiles].
 hipError_t launch_ssim_l1(const float* rgb, const float* target, int W, int H, float lam, float* dmaps,
                           float* partial, float* grad, const uint32_t* skip, hipStream_t s) {
@@ -325,9 +367,16 @@ hipError_t launch_ssim_l1(const float* rgb, const float* target, int W, int H, f
     const int64_t tiles = (int64_t)((W + kLossTile - 1) / kLossTile) * ((H + kLossTile - 1) / kLossTile) * 3;
     const dim3 grid((unsigned)((tiles + 7) & ~int64_t(7)));
     const float n = 3.0f * (float)W * (float)H;
-    hipLaunchKernelGGL(k_ssim_fwd, grid, dim3(256), 0, s, rgb, target, W, H, win, dmaps, partial, skip);
-    hipLaunchKernelGGL(k_ssim_bwd, grid, dim3(256), 0, s, rgb, target, W, H, win, dmaps, (1.0f - lam) / n, lam / n,
-                       grad, skip);
+#define LP_SSIM(NT_)                                                                                                \
+    hipLaunchKernelGGL(k_ssim_fwd<NT_>, grid, dim3(NT_), 0, s, rgb, target, W, H, win, dmaps, partial, skip);        \
+    hipLaunchKernelGGL(k_ssim_bwd<NT_>, grid, dim3(NT_), 0, s, rgb, target, W, H, win, dmaps, (1.0f - lam) / n,      \
+                       lam / n, grad, skip)
+    if (tiles <= kSsimFewTiles) {
+        LP_SSIM(512);
+    } else {
+        LP_SSIM(256);
+    }
+#undef LP_SSIM
     return hipGetLastError();
 }
 
