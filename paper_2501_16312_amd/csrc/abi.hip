@@ -48,6 +48,8 @@ ViewLayout view_layout(int64_t n, const linprim_camera* cams, int32_t n_views, i
     off = align256(off + (size_t)(((L.n_tiles_total + oi - 1) / oi) * kOrderClasses + 1) * 4);
     L.huge = off; off = align256(off + (size_t)vn * 4);
     L.trect = off; off = align256(off + (size_t)vn * 8);
+    L.tile_counts = off; off = align256(off + (size_t)counted_tiles(L.n_tiles_total) * 4);
+    L.tile_cursor = off; off = align256(off + (size_t)counted_tiles(L.n_tiles_total) * 4);
     L.total = off;
     return L;
 }

@@ -216,7 +216,19 @@ __global__ __launch_bounds__(256) void k_preprocess(const float* __restrict__ me
                                                     const ViewInfo* __restrict__ views, int n_views, int tile_shift,
                                                     int aa, float* __restrict__ payload,
                                                     uint32_t* __restrict__ depth_keys, uint32_t* __restrict__ tiles,
-                                                    uint2* __restrict__ trect, ViewChunk chunk) {
+                                                    uint2* __restrict__ trect, Status* __restrict__ status,
+                                                    uint32_t* __restrict__ tile_counts, int n_counts,
+                                                    ViewChunk chunk) {
+    // the lists the scan appends to start empty, and the tile counters at zero
+    // (the only state bin_sort's counting path expects; it leaves them so)
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        status->overflow = 0;
+        status->n_big = 0;
+        status->n_mid = 0;
+        status->n_huge = 0;
+    }
+    for (int g = (int)(blockIdx.x * blockDim.x + threadIdx.x); g < n_counts; g += (int)(gridDim.x * blockDim.x))
+        tile_counts[g] = 0u;
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     // BYVAL: the views (at most kViewChunk) come by value; the kernels after
     // this one read them from the workspace, where the first block stores them
@@ -283,9 +295,13 @@ hipError_t launch_preprocess(const linprim_prims& p, int32_t n_views, int tile, 
     uint32_t* keys = reinterpret_cast<uint32_t*>(ws + L.depth_keys);
     uint32_t* tiles = reinterpret_cast<uint32_t*>(ws + L.tiles);
     uint2* trect = reinterpret_cast<uint2*>(ws + L.trect);
+    Status* status = reinterpret_cast<Status*>(ws + L.status);
+    uint32_t* tile_counts = reinterpret_cast<uint32_t*>(ws + L.tile_counts);
+    const int n_counts = (int)counted_tiles(L.n_tiles_total);
 #define LP_PRE_K(K_, D_, E_, B_)                                                                            \
     hipLaunchKernelGGL((k_preprocess<K_, D_, E_, B_>), grid, dim3(256), 0, stream, p.means, p.quats, p.dists,   \
-                       p.opacity, p.sh, p.n, views, n_views, shift, aa ? 1 : 0, payload, keys, tiles, trect, chunk)
+                       p.opacity, p.sh, p.n, views, n_views, shift, aa ? 1 : 0, payload, keys, tiles, trect, status, \
+                       tile_counts, n_counts, chunk)
 #define LP_PRE(K_, D_)                                                                                     \
     do {                                                                                                     \
         if (exact) {                                                                                         \
@@ -351,14 +367,7 @@ __global__ void k_status_empty(Status* __restrict__ status) {
 
 __global__ __launch_bounds__(256) void k_scan_reduce(const uint32_t* __restrict__ in, int64_t count,
                                                      uint64_t* __restrict__ block_sums,
-                                                     uint64_t* __restrict__ vis_sums, Status* __restrict__ status) {
-    // the lists k_scan_apply appends to start empty
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
-        status->overflow = 0;
-        status->n_big = 0;
-        status->n_mid = 0;
-        status->n_huge = 0;
-    }
+                                                     uint64_t* __restrict__ vis_sums) {
     __shared__ uint64_t part[2][4];
     const int64_t base = (int64_t)blockIdx.x * kScanItems;
     uint64_t s = 0, c = 0;
@@ -464,6 +473,9 @@ __device__ inline void block_scan2_u64(uint64_t& a, uint64_t& b, uint64_t* part8
     b = pb + ib - b;
 }
 
+// Where k_scan_apply takes the totals of the blocks before each block from.
+enum : int { kTotalsBlocks = 0, kTotalsPrefixed = 1, kTotalsNone = 2 };
+
 // Also lists, in slot order, the slots that touch a tile (for the
 // preprocessing backward), and, in no particular order, those with more than
 // kBigRun gradient records (tile count x groups per tile) up to kHugeRun
@@ -475,7 +487,7 @@ __device__ inline void block_scan2_u64(uint64_t& a, uint64_t& b, uint64_t* part8
 __global__ __launch_bounds__(256) void k_scan_apply(const uint32_t* __restrict__ in, int64_t count,
                                                     const uint64_t* __restrict__ block_sums,
                                                     const uint64_t* __restrict__ vis_sums, int64_t nblocks,
-                                                    bool prefixed, uint32_t* __restrict__ out, int nq,
+                                                    int totals, uint32_t* __restrict__ out, int nq,
                                                     Status* __restrict__ status, uint32_t* __restrict__ big,
                                                     uint32_t* __restrict__ vis, uint32_t* __restrict__ huge) {
     constexpr int PER = kScanItems / 256;
@@ -486,11 +498,33 @@ __global__ __launch_bounds__(256) void k_scan_apply(const uint32_t* __restrict__
     __shared__ uint64_t part4[4];
     __shared__ uint64_t part8[8];
     // this block's start: the sums of the blocks before it (a few hundred
-    // values for a million slots), or the prefix k_scan_prefix wrote
+    // values for a million slots), the prefix k_scan_prefix wrote, or, with few
+    // blocks, the slots before it themselves
     uint64_t pre, vpre;
-    if (prefixed) {
+    if (totals == kTotalsPrefixed) {
         pre = block_sums[blockIdx.x];
         vpre = vis_sums[blockIdx.x];
+    } else if (totals == kTotalsNone) {
+        uint64_t s = 0;   // tile sum; visible slots from bit 44 on
+        const uint4* p = reinterpret_cast<const uint4*>(in);
+        for (int b = 0; b < (int)blockIdx.x; ++b) {
+            uint4 x[kScanItems / 1024];   // a block's slots: all loads in flight
+#pragma unroll
+            for (int k = 0; k < kScanItems / 1024; ++k) x[k] = p[b * (kScanItems / 4) + k * 256 + threadIdx.x];
+#pragma unroll
+            for (int k = 0; k < kScanItems / 1024; ++k) {
+                s += (uint64_t)x[k].x + x[k].y + x[k].z + x[k].w;
+                const uint32_t c = (x[k].x ? 1u : 0u) + (x[k].y ? 1u : 0u) + (x[k].z ? 1u : 0u) + (x[k].w ? 1u : 0u);
+                s += (uint64_t)c << 44;   // at most 32,768 slots of at most 2^24 tiles: no carry into it
+            }
+        }
+        for (int off = 32; off >= 1; off >>= 1) s += __shfl_xor(s, off, 64);
+        if ((threadIdx.x & 63) == 0) part4[threadIdx.x >> 6] = s;
+        __syncthreads();
+        s = part4[0] + part4[1] + part4[2] + part4[3];
+        __syncthreads();
+        pre = s & ((1ull << 44) - 1);
+        vpre = s >> 44;
     } else {
         pre = block_sum_u64(block_sums, blockIdx.x, part4);
         vpre = block_sum_u64(vis_sums, blockIdx.x, part4);
@@ -524,6 +558,10 @@ __global__ __launch_bounds__(256) void k_scan_apply(const uint32_t* __restrict__
     }
     uint64_t ts, tc;
     block_scan2_u64(s, c, part8, ts, tc);
+    if (totals == kTotalsNone && blockIdx.x == nblocks - 1 && t == 0) {
+        status->n_pairs = pre + ts;
+        status->n_vis = (uint32_t)(vpre + (uint32_t)tc);
+    }
     // the block's mid slots take one run of the mid list (a single atomic)
     __shared__ uint32_t mid_base;
     if (t == 0 && (tc >> 32)) mid_base = atomicAdd(&status->n_mid, (uint32_t)(tc >> 32));
@@ -565,11 +603,13 @@ hipError_t launch_scan(const ViewLayout& L, char* ws, int tile, hipStream_t stre
     const int64_t nb = L.scan_blocks;
     uint64_t* vsums = bsums + (nb + 1);
     if (nb > 0) {
-        hipLaunchKernelGGL(k_scan_reduce, dim3((unsigned)nb), dim3(256), 0, stream, tiles, count, bsums, vsums, status);
-        const bool prefixed = nb > kScanDirectBlocks;
-        if (prefixed) hipLaunchKernelGGL(k_scan_prefix, dim3(1), dim3(256), 0, stream, bsums, vsums, nb, status);
+        const int totals = nb <= kScanRecountBlocks ? kTotalsNone : nb <= kScanDirectBlocks ? kTotalsBlocks : kTotalsPrefixed;
+        if (totals != kTotalsNone)
+            hipLaunchKernelGGL(k_scan_reduce, dim3((unsigned)nb), dim3(256), 0, stream, tiles, count, bsums, vsums);
+        if (totals == kTotalsPrefixed)
+            hipLaunchKernelGGL(k_scan_prefix, dim3(1), dim3(256), 0, stream, bsums, vsums, nb, status);
         hipLaunchKernelGGL(k_scan_apply, dim3((unsigned)nb), dim3(256), 0, stream, tiles, count, bsums, vsums, nb,
-                           prefixed, offsets, nq, status, big, reinterpret_cast<uint32_t*>(ws + L.vis),
+                           totals, offsets, nq, status, big, reinterpret_cast<uint32_t*>(ws + L.vis),
                            reinterpret_cast<uint32_t*>(ws + L.huge));
     } else {
         hipLaunchKernelGGL(k_status_empty, dim3(1), dim3(64), 0, stream, status);

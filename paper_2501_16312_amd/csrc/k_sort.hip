@@ -12,12 +12,6 @@
 
 namespace linprim {
 
-__device__ inline void emit_pair(uint64_t g, uint32_t depth, uint32_t prim, uint32_t slot,
-                                 uint64_t* __restrict__ keys, uint32_t* __restrict__ vals) {
-    keys[slot] = (g << 32) | depth;
-    vals[slot] = prim;
-}
-
 // One thread per (view, primitive) slot that touches a tile (from the
 // scan's list, in slot order): one (key, value) pair per tile of the slot's
 // tile rectangle, row-major, at the slot's offset.  The short runs (at most
@@ -30,11 +24,36 @@ __device__ inline void emit_pair(uint64_t g, uint32_t depth, uint32_t prim, uint
 // the whole grid.
 constexpr uint32_t kShortRun = 32;
 
-__device__ inline void emit_wave(int64_t t, int64_t n_vis, const uint32_t* __restrict__ depth_keys,
+// What to do with a pair: global tile g, depth key, primitive, and the pair's
+// place in emission order.
+struct WritePair {
+    uint64_t* __restrict__ keys;
+    uint32_t* __restrict__ vals;
+    __device__ inline void operator()(uint64_t g, uint32_t depth, uint32_t prim, uint32_t place) const {
+        keys[place] = (g << 32) | depth;
+        vals[place] = prim;
+    }
+};
+struct CountPair {
+    uint32_t* bins;     // LDS, one per tile
+    __device__ inline void operator()(uint64_t g, uint32_t, uint32_t, uint32_t) const { atomicAdd(bins + g, 1u); }
+};
+struct PlacePair {
+    uint32_t* cursor;   // LDS, one per tile
+    uint64_t* __restrict__ keys;
+    uint32_t* __restrict__ vals;
+    __device__ inline void operator()(uint64_t g, uint32_t depth, uint32_t prim, uint32_t) const {
+        const uint32_t place = atomicAdd(cursor + g, 1u);
+        keys[place] = (g << 32) | depth;
+        vals[place] = prim;
+    }
+};
+
+template <class Pair>
+__device__ inline void emit_wave(const Pair& pair, int64_t t, int64_t n_vis, const uint32_t* __restrict__ depth_keys,
                                  const uint32_t* __restrict__ tiles, const uint32_t* __restrict__ offsets,
                                  const uint2* __restrict__ trect, const ViewInfo* __restrict__ views,
-                                 const uint32_t* __restrict__ vis, int64_t n,
-                                 uint64_t* __restrict__ keys, uint32_t* __restrict__ vals) {
+                                 const uint32_t* __restrict__ vis, int64_t n) {
     const int lane = threadIdx.x & 63;
     uint32_t cnt = 0, key = 0, off = 0, prim = 0, ntx = 1, tiles_x = 0;
     uint64_t g0 = 0;                  // global tile of the rectangle's first tile
@@ -77,9 +96,7 @@ __device__ inline void emit_wave(int64_t t, int64_t n_vis, const uint32_t* __res
                             (uint32_t)__shfl((int)(uint32_t)g0, lo, 64);
         if (q < total) {
             const uint32_t row = r / bn, col = r - row * bn;
-            const uint64_t g = bg + (uint64_t)row * btx + col;
-            keys[bo + r] = (g << 32) | bk;
-            vals[bo + r] = bp;
+            pair(bg + (uint64_t)row * btx + col, bk, bp, bo + r);
         }
     }
     // long runs: the whole wavefront writes each (huge ones are left to
@@ -98,37 +115,25 @@ __device__ inline void emit_wave(int64_t t, int64_t n_vis, const uint32_t* __res
                             (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)g0, b);
         for (uint32_t q = (uint32_t)lane; q < c; q += 64) {
             const uint32_t row = q / bn, col = q - row * bn;
-            keys[o + q] = ((bg + (uint64_t)row * btx + col) << 32) | k;
-            vals[o + q] = pb;
+            pair(bg + (uint64_t)row * btx + col, k, pb, o + q);
         }
     }
 }
 
-__global__ __launch_bounds__(256) void k_emit_pairs(const uint32_t* __restrict__ depth_keys,
-                                                    const uint32_t* __restrict__ tiles,
-                                                    const uint32_t* __restrict__ offsets,
-                                                    const uint2* __restrict__ trect,
-                                                    const ViewInfo* __restrict__ views, const uint32_t* __restrict__ vis,
-                                                    int64_t n, Status* __restrict__ status,
-                                                    uint64_t capacity, const uint32_t* __restrict__ huge,
-                                                    uint64_t* __restrict__ keys, uint32_t* __restrict__ vals,
-                                                    uint2* __restrict__ ranges, int64_t n_tiles) {
+// Every pair of every visible slot, by the whole grid.
+template <class Pair>
+__device__ inline void emit_all(const Pair& pair, const uint32_t* __restrict__ depth_keys,
+                                const uint32_t* __restrict__ tiles, const uint32_t* __restrict__ offsets,
+                                const uint2* __restrict__ trect, const ViewInfo* __restrict__ views,
+                                const uint32_t* __restrict__ vis, int64_t n, const Status* __restrict__ status,
+                                const uint32_t* __restrict__ huge) {
     const int lane = threadIdx.x & 63;
-    // the tile ranges start empty (k_tile_ranges fills them after the sort)
-    for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < n_tiles; t += (int64_t)gridDim.x * blockDim.x)
-        ranges[t] = make_uint2(0u, 0u);
-    if (blockIdx.x == 0 && threadIdx.x == 0) status->n_long = 0u;
-    const uint64_t npairs = status->n_pairs;
-    if (npairs > capacity) {
-        if (blockIdx.x == 0 && threadIdx.x == 0) status->overflow = 1;
-        return;
-    }
     const int64_t n_vis = status->n_vis;
     // a grid of a few waves per CU strides over the list, 64 slots at a time
     const int64_t n_waves = (int64_t)gridDim.x * (blockDim.x >> 6);
     const int64_t wave_id = (int64_t)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
     for (int64_t w0 = wave_id * 64; w0 < n_vis; w0 += n_waves * 64)
-        emit_wave(w0 + lane, n_vis, depth_keys, tiles, offsets, trect, views, vis, n, keys, vals);
+        emit_wave(pair, w0 + lane, n_vis, depth_keys, tiles, offsets, trect, views, vis, n);
     // huge runs: 64-pair chunks dealt round-robin over all waves
     const uint32_t n_huge = status->n_huge;
     for (uint32_t i = 0; i < n_huge; ++i) {
@@ -145,11 +150,93 @@ __global__ __launch_bounds__(256) void k_emit_pairs(const uint32_t* __restrict__
             const uint32_t q = (uint32_t)q0 + (uint32_t)lane;
             if (q < c) {
                 const uint32_t row = q / bn, col = q - row * bn;
-                keys[o + q] = ((bg + (uint64_t)row * (uint32_t)V.tiles_x + col) << 32) | k;
-                vals[o + q] = prim;
+                pair(bg + (uint64_t)row * (uint32_t)V.tiles_x + col, k, prim, o + q);
             }
         }
     }
+}
+
+__global__ __launch_bounds__(256) void k_emit_pairs(const uint32_t* __restrict__ depth_keys,
+                                                    const uint32_t* __restrict__ tiles,
+                                                    const uint32_t* __restrict__ offsets,
+                                                    const uint2* __restrict__ trect,
+                                                    const ViewInfo* __restrict__ views, const uint32_t* __restrict__ vis,
+                                                    int64_t n, Status* __restrict__ status,
+                                                    uint64_t capacity, const uint32_t* __restrict__ huge,
+                                                    uint64_t* __restrict__ keys, uint32_t* __restrict__ vals,
+                                                    uint2* __restrict__ ranges, int64_t n_tiles) {
+    // the tile ranges start empty (k_tile_ranges fills them after the sort)
+    for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < n_tiles; t += (int64_t)gridDim.x * blockDim.x)
+        ranges[t] = make_uint2(0u, 0u);
+    if (blockIdx.x == 0 && threadIdx.x == 0) status->n_long = 0u;
+    if (status->n_pairs > capacity) {
+        if (blockIdx.x == 0 && threadIdx.x == 0) status->overflow = 1;
+        return;
+    }
+    emit_all(WritePair{keys, vals}, depth_keys, tiles, offsets, trect, views, vis, n, status, huge);
+}
+
+// ---------------------------------------------------------------------------
+// Binning by tile counters, for at most kPlanTiles tiles and kPlacePairs
+// pairs: count every tile's pairs, turn the counts into ranges, cursors and
+// render orders in one block, place every pair at its tile's cursor.  Pairs of
+// a tile land in any order; the list sort that follows orders them by (depth,
+// primitive), which is unique within a tile, so the result is that of the
+// radix passes.  Three launches instead of nine, most of them too small to
+// fill the chip.  The blocks count in LDS and add to a tile's global counter
+// once, so that a tile that thousands of pairs touch costs it at most
+// kBinBlocks atomics (an atomic per pair: 45 ns each on one address, 280 us
+// instead of 149 with 830 pairs on each of 49 tiles).
+// ---------------------------------------------------------------------------
+constexpr int kBinThreads = 512;
+constexpr int64_t kBinBlocks = 128;
+
+__global__ __launch_bounds__(kBinThreads) void k_count_tiles(const uint32_t* __restrict__ depth_keys,
+                                                             const uint32_t* __restrict__ tiles,
+                                                             const uint32_t* __restrict__ offsets,
+                                                             const uint2* __restrict__ trect,
+                                                             const ViewInfo* __restrict__ views,
+                                                             const uint32_t* __restrict__ vis, int64_t n,
+                                                             Status* __restrict__ status, uint64_t capacity,
+                                                             const uint32_t* __restrict__ huge, int n_tiles,
+                                                             uint32_t* __restrict__ counts) {
+    extern __shared__ uint32_t bins[];
+    if (blockIdx.x == 0 && threadIdx.x == 0) status->n_long = 0u;
+    if (status->n_pairs > capacity) {
+        if (blockIdx.x == 0 && threadIdx.x == 0) status->overflow = 1;
+        return;
+    }
+    if ((int64_t)blockIdx.x * kBinThreads >= (int64_t)status->n_vis && status->n_huge == 0) return;
+    for (int g = threadIdx.x; g < n_tiles; g += kBinThreads) bins[g] = 0u;
+    __syncthreads();
+    emit_all(CountPair{bins}, depth_keys, tiles, offsets, trect, views, vis, n, status, huge);
+    __syncthreads();
+    for (int g = threadIdx.x; g < n_tiles; g += kBinThreads)
+        if (bins[g]) atomicAdd(counts + g, bins[g]);
+}
+
+__global__ __launch_bounds__(kBinThreads) void k_place_pairs(const uint32_t* __restrict__ depth_keys,
+                                                             const uint32_t* __restrict__ tiles,
+                                                             const uint32_t* __restrict__ offsets,
+                                                             const uint2* __restrict__ trect,
+                                                             const ViewInfo* __restrict__ views,
+                                                             const uint32_t* __restrict__ vis, int64_t n,
+                                                             const Status* __restrict__ status, uint64_t capacity,
+                                                             const uint32_t* __restrict__ huge, int n_tiles,
+                                                             uint32_t* __restrict__ cursor,
+                                                             uint64_t* __restrict__ keys, uint32_t* __restrict__ vals) {
+    extern __shared__ uint32_t bins[];
+    if (status->n_pairs > capacity) return;
+    if ((int64_t)blockIdx.x * kBinThreads >= (int64_t)status->n_vis && status->n_huge == 0) return;
+    for (int g = threadIdx.x; g < n_tiles; g += kBinThreads) bins[g] = 0u;
+    __syncthreads();
+    emit_all(CountPair{bins}, depth_keys, tiles, offsets, trect, views, vis, n, status, huge);
+    __syncthreads();
+    // the block's run of every tile it touches
+    for (int g = threadIdx.x; g < n_tiles; g += kBinThreads)
+        if (bins[g]) bins[g] = atomicAdd(cursor + g, bins[g]);
+    __syncthreads();
+    emit_all(PlacePair{bins, keys, vals}, depth_keys, tiles, offsets, trect, views, vis, n, status, huge);
 }
 
 // ---------------------------------------------------------------------------
@@ -688,6 +775,98 @@ __device__ inline int order_group(int c) {
     return g;
 }
 
+// One block: the tiles' counts (left at zero for the next bin_sort) to their
+// ranges and cursors, and both render orders as k_order_write defines them.
+// Thread t takes tiles t, t + 1024, ..., all loads in flight together; a wave
+// leaves, per round, its pairs and its tiles of each class and group (ranked
+// by ballots); one thread per quantity then turns those into exclusive
+// prefixes over rounds and waves, so that the block waits twice in all.
+__global__ __launch_bounds__(1024) void k_plan_tiles(uint32_t* __restrict__ counts, int n_tiles,
+                                                     const Status* __restrict__ status, uint64_t capacity,
+                                                     uint32_t* __restrict__ cursor, uint2* __restrict__ ranges,
+                                                     uint32_t* __restrict__ order_fwd,
+                                                     uint32_t* __restrict__ order_bwd) {
+    constexpr int K = kOrderClasses, G = kFwdGroups, Q = K + G + 1, NW = 16, R = (int)(kPlanTiles / 1024);
+    // [round * NW + wave][quantity]: tiles of the classes, of the groups, pairs
+    __shared__ uint32_t part[R * NW][Q];
+    __shared__ uint32_t total[Q];
+    if (status->n_pairs > capacity) return;
+    const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+    const uint64_t lt_mask = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
+    const int rounds = (n_tiles + 1023) / 1024;
+    uint32_t len[R], excl[R], rank[R], grank[R];   // pairs, pairs before in the wave, rank in class and group
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const int g = r * 1024 + t;
+        len[r] = g < n_tiles ? counts[g] : 0u;
+    }
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        if (r >= rounds) break;
+        const bool valid = r * 1024 + t < n_tiles;
+        uint32_t* row = part[r * NW + wave];
+        const uint32_t incl = wave_incl_scan_u32(len[r]);
+        excl[r] = incl - len[r];
+        const int c = valid ? order_class(len[r]) : 0, grp = order_group(c);
+        uint64_t peers = __ballot(valid);
+#pragma unroll
+        for (int bit = 0; bit < 4; ++bit) {
+            const uint64_t m = __ballot(valid && ((c >> bit) & 1));
+            peers &= ((c >> bit) & 1) ? m : ~m;
+        }
+        if (lane < K) row[lane] = 0u;
+        uint64_t gm = 0;
+#pragma unroll
+        for (int k = 0; k < G; ++k) {
+            const uint64_t m = __ballot(valid && grp == k);
+            if (lane == 0) row[K + k] = (uint32_t)__popcll(m);
+            gm = (grp == k) ? m : gm;
+        }
+        if (lane == 63) row[K + G] = incl;
+        rank[r] = (uint32_t)__popcll(peers & lt_mask);
+        grank[r] = (uint32_t)__popcll(gm & lt_mask);
+        if (valid && rank[r] == 0) row[c] = (uint32_t)__popcll(peers);
+    }
+    __syncthreads();
+    if (t < Q) {
+        uint32_t run = 0;
+        for (int w = 0; w < rounds * NW; ++w) {
+            const uint32_t x = part[w][t];
+            part[w][t] = run;
+            run += x;
+        }
+        total[t] = run;
+    }
+    __syncthreads();
+    // tiles of the classes before each class
+    uint32_t before[K];
+    uint32_t acc = 0;
+#pragma unroll
+    for (int c = 0; c < K; ++c) {
+        before[c] = acc;
+        acc += total[c];
+    }
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const int g = r * 1024 + t;
+        if (g >= n_tiles) break;
+        const uint32_t* row = part[r * NW + wave];
+        const uint32_t start = row[K + G] + excl[r];
+        counts[g] = 0u;
+        cursor[g] = start;
+        ranges[g] = len[r] ? make_uint2(start, start + len[r]) : make_uint2(0u, 0u);
+        const int c = order_class(len[r]), grp = order_group(c);
+        uint32_t cb = 0, gb = 0;
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            cb = (c == k) ? before[k] : cb;
+            if (k == 0 || order_group(k - 1) != order_group(k)) gb = (grp == order_group(k)) ? before[k] : gb;
+        }
+        order_bwd[cb + row[c] + rank[r]] = (uint32_t)g;
+        order_fwd[gb + row[K + grp] + grank[r]] = (uint32_t)g;
+    }
+}
+
 __global__ __launch_bounds__(256) void k_order_write(const uint2* __restrict__ ranges, int64_t n_tiles,
                                                      const Status* __restrict__ status, uint64_t capacity,
                                                      const uint32_t* __restrict__ sums, int64_t nblocks,
@@ -823,21 +1002,6 @@ hipError_t launch_bin_sort(const ViewLayout& L, char* vws, const PairLayout& P, 
     uint32_t* long_list = reinterpret_cast<uint32_t*>(vws + L.long_list);
     const uint64_t cap = (uint64_t)P.capacity;
     const int64_t nt = L.n_tiles_total;
-    if (L.n > 0) {
-        const int64_t vn = L.n * (int64_t)n_views;
-        // enough 4-wave blocks for the list, at most 2048 (32 waves per CU)
-        const int64_t blocks = (vn + 255) / 256 < 2048 ? (vn + 255) / 256 : 2048;
-        hipLaunchKernelGGL(k_emit_pairs, dim3((unsigned)blocks), dim3(256), 0, stream,
-                           reinterpret_cast<const uint32_t*>(vws + L.depth_keys),
-                           reinterpret_cast<const uint32_t*>(vws + L.tiles),
-                           reinterpret_cast<const uint32_t*>(vws + L.offsets),
-                           reinterpret_cast<const uint2*>(vws + L.trect), views,
-                           reinterpret_cast<const uint32_t*>(vws + L.vis), L.n, status, cap,
-                           reinterpret_cast<const uint32_t*>(vws + L.huge), ka, va, ranges, nt);
-    } else {
-        hipLaunchKernelGGL(k_clear_ranges, dim3((unsigned)((nt + 255) / 256)), dim3(256), 0, stream, ranges, nt,
-                           status);
-    }
     const int tb = key_tile_bits(nt);
     int passes, digit, key_lo, key_bits;
     if (radix) {
@@ -852,41 +1016,76 @@ hipError_t launch_bin_sort(const ViewLayout& L, char* vws, const PairLayout& P, 
     }
     uint64_t *kin = ka, *kout = kb;
     uint32_t *vin = va, *vout = vb;
-    const int64_t nb = P.sort_blocks;
-    for (int p = 0; p < passes; ++p) {
-        const int sh = p * digit;
-        const int bits = (key_bits - sh) < digit ? (key_bits - sh) : digit;
-        if (nb > 0) {
-            hipLaunchKernelGGL(k_radix_hist, dim3((unsigned)nb), dim3(kSortThreads), 0, stream, kin, status, cap,
-                               key_lo + sh, bits, nb, hist);
-            hipLaunchKernelGGL(k_radix_scan, dim3(1u << bits), dim3(1024), 0, stream, hist, status, cap, nb, totals);
-            hipLaunchKernelGGL(k_radix_scatter, dim3((unsigned)nb), dim3(kSortThreads), 0, stream, kin, vin, status,
-                               cap, key_lo + sh, bits, nb, hist, totals, kout, vout);
+    uint32_t* order = reinterpret_cast<uint32_t*>(vws + L.order);
+    uint32_t* order_bwd = reinterpret_cast<uint32_t*>(vws + L.order_bwd);
+    const uint32_t* depth_keys = reinterpret_cast<const uint32_t*>(vws + L.depth_keys);
+    const uint32_t* tiles = reinterpret_cast<const uint32_t*>(vws + L.tiles);
+    const uint32_t* offsets = reinterpret_cast<const uint32_t*>(vws + L.offsets);
+    const uint2* trect = reinterpret_cast<const uint2*>(vws + L.trect);
+    const uint32_t* vis = reinterpret_cast<const uint32_t*>(vws + L.vis);
+    const uint32_t* huge = reinterpret_cast<const uint32_t*>(vws + L.huge);
+    // enough 4-wave blocks for the visible list, at most 2048 (32 waves per CU)
+    const int64_t vn = L.n * (int64_t)n_views;
+    const unsigned emit_blocks = (unsigned)((vn + 255) / 256 < 2048 ? (vn + 255) / 256 : 2048);
+    if (!radix && L.n > 0 && nt <= kPlanTiles && P.capacity <= kPlacePairs) {
+        uint32_t* counts = reinterpret_cast<uint32_t*>(vws + L.tile_counts);
+        uint32_t* cursor = reinterpret_cast<uint32_t*>(vws + L.tile_cursor);
+        // the list sort writes the buffer that sorted_buffer() names
+        if (passes & 1) {
+            kin = kb; kout = ka;
+            vin = vb; vout = va;
         }
-        uint64_t* tk = kin; kin = kout; kout = tk;
-        uint32_t* tv = vin; vin = vout; vout = tv;
-    }
-    if (P.capacity > 0)
-        hipLaunchKernelGGL(k_tile_ranges, dim3((unsigned)((P.capacity + 255) / 256)), dim3(256), 0, stream, kin, status,
-                           cap, ranges);
-    {
-        uint32_t* order = reinterpret_cast<uint32_t*>(vws + L.order);
-        uint32_t* order_bwd = reinterpret_cast<uint32_t*>(vws + L.order_bwd);
-        uint32_t* osums = reinterpret_cast<uint32_t*>(vws + L.order_sums);
-        const int items = order_items(nt);
-        const int64_t ob = (nt + items - 1) / items;
-        hipLaunchKernelGGL(k_order_count, dim3((unsigned)ob), dim3(256), 0, stream, ranges, nt, status, cap, osums,
-                           items);
-        const bool prefixed = ob > kOrderDirectBlocks;
-        if (prefixed)
-            hipLaunchKernelGGL(k_order_prefix, dim3(1), dim3(1024), 0, stream, osums, ob * kOrderClasses, status, cap);
-        hipLaunchKernelGGL(k_order_write, dim3((unsigned)ob), dim3(256), 0, stream, ranges, nt, status, cap, osums, ob,
-                           prefixed, order, order_bwd, items);
+        const int64_t bb = (vn + kBinThreads - 1) / kBinThreads;
+        const dim3 bin_grid((unsigned)(bb < kBinBlocks ? bb : kBinBlocks));
+        const unsigned lds = (unsigned)nt * 4;
+        hipLaunchKernelGGL(k_count_tiles, bin_grid, dim3(kBinThreads), lds, stream, depth_keys, tiles, offsets, trect,
+                           views, vis, L.n, status, cap, huge, (int)nt, counts);
+        hipLaunchKernelGGL(k_plan_tiles, dim3(1), dim3(1024), 0, stream, counts, (int)nt, status, cap, cursor, ranges,
+                           order, order_bwd);
+        hipLaunchKernelGGL(k_place_pairs, bin_grid, dim3(kBinThreads), lds, stream, depth_keys, tiles, offsets, trect,
+                           views, vis, L.n, status, cap, huge, (int)nt, cursor, kin, vin);
+    } else {
+        if (L.n > 0) {
+            hipLaunchKernelGGL(k_emit_pairs, dim3(emit_blocks), dim3(256), 0, stream, depth_keys, tiles, offsets,
+                               trect, views, vis, L.n, status, cap, huge, ka, va, ranges, nt);
+        } else {
+            hipLaunchKernelGGL(k_clear_ranges, dim3((unsigned)((nt + 255) / 256)), dim3(256), 0, stream, ranges, nt,
+                               status);
+        }
+        const int64_t nb = P.sort_blocks;
+        for (int p = 0; p < passes; ++p) {
+            const int sh = p * digit;
+            const int bits = (key_bits - sh) < digit ? (key_bits - sh) : digit;
+            if (nb > 0) {
+                hipLaunchKernelGGL(k_radix_hist, dim3((unsigned)nb), dim3(kSortThreads), 0, stream, kin, status, cap,
+                                   key_lo + sh, bits, nb, hist);
+                hipLaunchKernelGGL(k_radix_scan, dim3(1u << bits), dim3(1024), 0, stream, hist, status, cap, nb, totals);
+                hipLaunchKernelGGL(k_radix_scatter, dim3((unsigned)nb), dim3(kSortThreads), 0, stream, kin, vin, status,
+                                   cap, key_lo + sh, bits, nb, hist, totals, kout, vout);
+            }
+            uint64_t* tk = kin; kin = kout; kout = tk;
+            uint32_t* tv = vin; vin = vout; vout = tv;
+        }
+        if (P.capacity > 0)
+            hipLaunchKernelGGL(k_tile_ranges, dim3((unsigned)((P.capacity + 255) / 256)), dim3(256), 0, stream, kin, status,
+                               cap, ranges);
+        {
+            uint32_t* osums = reinterpret_cast<uint32_t*>(vws + L.order_sums);
+            const int items = order_items(nt);
+            const int64_t ob = (nt + items - 1) / items;
+            hipLaunchKernelGGL(k_order_count, dim3((unsigned)ob), dim3(256), 0, stream, ranges, nt, status, cap, osums,
+                               items);
+            const bool prefixed = ob > kOrderDirectBlocks;
+            if (prefixed)
+                hipLaunchKernelGGL(k_order_prefix, dim3(1), dim3(1024), 0, stream, osums, ob * kOrderClasses, status, cap);
+            hipLaunchKernelGGL(k_order_write, dim3((unsigned)ob), dim3(256), 0, stream, ranges, nt, status, cap, osums, ob,
+                               prefixed, order, order_bwd, items);
+        }
     }
     if (!radix) {
         // per-list sort from (kin, vin) into (kout, vout)
         hipLaunchKernelGGL(k_sort_short_lists, dim3((unsigned)nt), dim3(64), 0, stream, ranges, nt, status, cap, kin,
-                           vin, kout, vout, long_list, reinterpret_cast<const uint32_t*>(vws + L.order_bwd));
+                           vin, kout, vout, long_list, order_bwd);
         const int64_t lblocks = nt < 512 ? nt : 512;
         hipLaunchKernelGGL(k_sort_long_lists, dim3((unsigned)lblocks), dim3(256), 0, stream, ranges, long_list, status,
                            cap, kin, vin, kout, vout);

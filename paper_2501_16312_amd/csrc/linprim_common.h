@@ -90,9 +90,20 @@ struct Status {
 // Offsets into the view workspace (all 256-byte aligned).
 struct ViewLayout {
     size_t status, views, payload, depth_keys, tiles, offsets, block_sums, ranges, big, long_list, vis, stats, order,
-        order_bwd, order_sums, huge, trect, total;
+        order_bwd, order_sums, huge, trect, tile_counts, tile_cursor, total;
     int64_t n, n_views, n_tiles_total, scan_blocks;
 };
+
+// Binning by tile counters (bin_sort's small path): up to this many tiles, one
+// block turns the counts into ranges and render orders, 1024 tiles a round.
+constexpr int64_t kPlanTiles = 8192;
+// ... and up to this many pairs (bin_sort, all launches, against emission, two
+// tile-bit radix passes, ranges and orders): 18k pairs 22 us against 41, 64k 32
+// against 43, 81k 35 against 49, 103k (most in runs of many tiles) 50 against
+// 50; with an atomic per pair instead of one per block and tile, 220k pairs
+// took 57 us of kernel time against 43.
+constexpr int64_t kPlacePairs = 131072;
+inline int64_t counted_tiles(int64_t n_tiles) { return n_tiles <= kPlanTiles ? n_tiles : 0; }
 
 // Offsets into the pair workspace.
 struct PairLayout {
@@ -105,6 +116,10 @@ constexpr int kScanItems = 4096;     // elements per scan block (256 threads x 1
 // before it itself (8192 blocks: 32M slots); beyond, a single block turns
 // the totals into prefixes first.
 constexpr int64_t kScanDirectBlocks = 8192;
+// Up to this many, a block of the scan reads the slots before its own instead
+// of their block totals, and the kernel that forms those is not launched (at
+// most 28 16-byte loads per thread, less than a launch).
+constexpr int64_t kScanRecountBlocks = 8;
 // Tiles per block of the render order kernels (256 threads x 4), and the
 // same choice for their per-block counts (256 blocks: 256K tiles).
 constexpr int64_t kOrderDirectBlocks = 256;
