@@ -430,19 +430,6 @@ __device__ inline uint64_t block_sum_u64(const uint64_t* __restrict__ x, int64_t
     return part4[0] + part4[1] + part4[2] + part4[3];
 }
 
-// Appends a slot to a list (in no particular order) with one atomic per
-// wave and item.
-__device__ inline void wave_append(bool take, uint32_t value, uint32_t* __restrict__ counter,
-                                   uint32_t* __restrict__ list, int lane, uint64_t lt_mask) {
-    const uint64_t m = __ballot(take);
-    if (!m) return;
-    const int leader = __builtin_ctzll(m);
-    uint32_t first = 0;
-    if (lane == leader) first = atomicAdd(counter, (uint32_t)__popcll(m));
-    first = __shfl(first, leader, 64);
-    if (take) list[first + __popcll(m & lt_mask)] = value;
-}
-
 // Exclusive scan of two counters over the 256 threads of a block (wave
 // shuffles, then the four wave totals); a and b become the sums over the
 // threads before this one, ta and tb the block totals.
@@ -477,11 +464,14 @@ __device__ inline void block_scan2_u64(uint64_t& a, uint64_t& b, uint64_t* part8
 enum : int { kTotalsBlocks = 0, kTotalsPrefixed = 1, kTotalsNone = 2 };
 
 // Also lists, in slot order, the slots that touch a tile (for the
-// preprocessing backward), and, in no particular order, those with more than
-// kBigRun gradient records (tile count x groups per tile) up to kHugeRun
-// tiles and those with more than kHugeRun tiles; per block in slot order, the slots with more
-// than kMidRun up to kBigRun records (the mid list, from the end of the big
-// list's array).  The block's counts are loaded and its offsets
+// preprocessing backward), and, in slot order within a block, those with more
+// than kBigRun gradient records (tile count x groups per tile) up to kHugeRun
+// tiles, those with more than kHugeRun tiles, and those with more than kMidRun
+// up to kBigRun records (the mid list, from the end of the big list's array):
+// one atomic per block and list, so that no wave waits for one atomic after
+// another (16-pixel tiles, where a slot of 17 tiles is on the big list, 500k
+// slots, a few of them hundreds of tiles wide: 30 us with one atomic per wave
+// and item, 11 now).  The block's counts are loaded and its offsets
 // and list entries stored coalesced, through LDS; each thread scans 16
 // consecutive slots in between.
 __global__ __launch_bounds__(256) void k_scan_apply(const uint32_t* __restrict__ in, int64_t count,
@@ -543,42 +533,44 @@ __global__ __launch_bounds__(256) void k_scan_apply(const uint32_t* __restrict__
     }
     __syncthreads();
     uint32_t v[PER];
-    // per thread: tile sum; slots that touch a tile (low word) and mid slots
-    // (high word), scanned together
+    // per thread: tile sum; slots that touch a tile, mid, big and huge slots,
+    // 16 bits each (a block has 4096), scanned together
     uint64_t s = 0, c = 0;
+    auto is_huge = [](uint32_t x) { return x > (uint32_t)kHugeRun; };
     auto is_mid = [nq](uint32_t x) {
         const int64_t nrec = (int64_t)x * nq;
         return nrec > kMidRun && nrec <= kBigRun;
     };
+    // (slots over kHugeRun tiles are on the huge list, which also serves
+    // their record sums)
+    auto is_big = [nq](uint32_t x) { return (int64_t)x * nq > kBigRun && x <= (uint32_t)kHugeRun; };
 #pragma unroll
     for (int k = 0; k < PER; ++k) {
         v[k] = stage[t * (PER + 1) + k];
         s += v[k];
-        c += (v[k] ? 1u : 0u) + (is_mid(v[k]) ? (1ull << 32) : 0ull);
+        c += (v[k] ? 1ull : 0ull) + (is_mid(v[k]) ? (1ull << 16) : 0ull) + (is_big(v[k]) ? (1ull << 32) : 0ull) +
+             (is_huge(v[k]) ? (1ull << 48) : 0ull);
     }
     uint64_t ts, tc;
     block_scan2_u64(s, c, part8, ts, tc);
     if (totals == kTotalsNone && blockIdx.x == nblocks - 1 && t == 0) {
         status->n_pairs = pre + ts;
-        status->n_vis = (uint32_t)(vpre + (uint32_t)tc);
+        status->n_vis = (uint32_t)(vpre + (tc & 0xffffu));
     }
-    // the block's mid slots take one run of the mid list (a single atomic)
-    __shared__ uint32_t mid_base;
-    if (t == 0 && (tc >> 32)) mid_base = atomicAdd(&status->n_mid, (uint32_t)(tc >> 32));
+    // the block's mid, big and huge slots take one run of their list each
+    __shared__ uint32_t list_base[3];
+    if (t < 3) {
+        const uint32_t m = (uint32_t)(tc >> (16 * (t + 1))) & 0xffffu;
+        uint32_t* counter = t == 0 ? &status->n_mid : t == 1 ? &status->n_big : &status->n_huge;
+        list_base[t] = m ? atomicAdd(counter, m) : 0u;
+    }
     uint64_t run = pre + s;
-    uint32_t lv = (uint32_t)c, lm = (uint32_t)(c >> 32);
-    const int lane = t & 63;
-    const uint64_t lt_mask = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
+    uint32_t lv = (uint32_t)c & 0xffffu;
 #pragma unroll
     for (int k = 0; k < PER; ++k) {
-        const uint32_t idx = (uint32_t)(base + (int64_t)t * PER + k);
         stage[t * (PER + 1) + k] = (uint32_t)run;
         run += v[k];
-        if (v[k]) vstage[lv++] = idx;
-        // (slots over kHugeRun tiles are on the huge list, which also serves
-        // their record sums)
-        wave_append((int64_t)v[k] * nq > kBigRun && v[k] <= (uint32_t)kHugeRun, idx, &status->n_big, big, lane, lt_mask);
-        wave_append(v[k] > (uint32_t)kHugeRun, idx, &status->n_huge, huge, lane, lt_mask);
+        if (v[k]) vstage[lv++] = (uint32_t)(base + (int64_t)t * PER + k);
     }
     __syncthreads();
 #pragma unroll
@@ -586,10 +578,20 @@ __global__ __launch_bounds__(256) void k_scan_apply(const uint32_t* __restrict__
         const int e = k * 256 + t;
         const int64_t idx = base + e;
         if (idx < count) out[idx] = stage[e + e / PER];
-        const int64_t own = base + (int64_t)t * PER + k;
-        if (is_mid(v[k])) big[count - 1 - (int64_t)(mid_base + lm++)] = (uint32_t)own;
     }
-    for (int j = t; j < (int)(uint32_t)tc; j += 256) vis[vpre + j] = vstage[j];
+    for (int j = t; j < (int)(tc & 0xffffu); j += 256) vis[vpre + j] = vstage[j];
+    if (tc >> 16) {
+        uint32_t lm = list_base[0] + ((uint32_t)(c >> 16) & 0xffffu);
+        uint32_t lb = list_base[1] + ((uint32_t)(c >> 32) & 0xffffu);
+        uint32_t lh = list_base[2] + ((uint32_t)(c >> 48) & 0xffffu);
+#pragma unroll
+        for (int k = 0; k < PER; ++k) {
+            const uint32_t own = (uint32_t)(base + (int64_t)t * PER + k);
+            if (is_mid(v[k])) big[count - 1 - (int64_t)lm++] = own;
+            if (is_big(v[k])) big[lb++] = own;
+            if (is_huge(v[k])) huge[lh++] = own;
+        }
+    }
 }
 
 hipError_t launch_scan(const ViewLayout& L, char* ws, int tile, hipStream_t stream) {
