@@ -1,8 +1,13 @@
 // abi.hip -- the extern "C" entry points of liblinprim.so: argument
 // validation, workspace layouts and launch order.  Every call enqueues on
 // the caller's stream; only linprim_pair_count / linprim_read_status wait.
+#include <stddef.h>
 #include <stdlib.h>
 #include <string.h>
+
+#include <atomic>
+#include <chrono>
+#include <mutex>
 
 #include "linprim_common.h"
 
@@ -81,6 +86,100 @@ hipError_t launch_render_fwd_ex(const ViewLayout& L, const char* vws, const Pair
 using namespace linprim;
 
 namespace {
+
+// ---------------------------------------------------------------------------
+// Reading a few device words back.  A kernel writes them, then a sequence
+// number, into pinned host memory that the caller polls: 7.5 us with an idle
+// stream, where a copy to pageable memory and a stream synchronisation took
+// 22.  The slots come from one pinned page, kept until the process ends; a call
+// holds one slot while it waits, so threads and streams do not share any.
+// Whatever stands in the way (no free slot, no pinned memory, a launch that
+// fails, a wait of more than kPollMicros) ends in the copy and the
+// synchronisation, which also report the stream's errors.
+// ---------------------------------------------------------------------------
+constexpr int kReadWords = 2;
+constexpr int kReadSlots = 64;
+constexpr int kPollMicros = 500;
+
+struct alignas(64) ReadSlot {
+    uint64_t seq;
+    uint64_t word[kReadWords];
+};
+
+__global__ void k_read_back(const uint64_t* __restrict__ src, int words, ReadSlot* slot, uint64_t seq) {
+    if (threadIdx.x != 0) return;
+    for (int k = 0; k < words; ++k)
+        __hip_atomic_store(&slot->word[k], src[k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    __hip_atomic_store(&slot->seq, seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
+std::mutex g_read_mu;
+ReadSlot* g_read_page;
+bool g_read_tried;
+uint64_t g_read_used;                  // slots in use, a bit each
+std::atomic<uint64_t> g_read_seq{1};   // a slot's number never comes twice
+
+ReadSlot* take_slot() {
+    std::lock_guard<std::mutex> lock(g_read_mu);
+    if (!g_read_tried) {
+        g_read_tried = true;
+        void* p = nullptr;
+        // relaxed: another thread's capture is not disturbed by the allocation
+        hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+        const bool swapped = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
+        if (hipHostMalloc(&p, sizeof(ReadSlot) * kReadSlots, hipHostMallocPortable | hipHostMallocMapped) == hipSuccess) {
+            memset(p, 0, sizeof(ReadSlot) * kReadSlots);
+            g_read_page = static_cast<ReadSlot*>(p);
+        } else {
+            (void)hipGetLastError();
+        }
+        if (swapped) (void)hipThreadExchangeStreamCaptureMode(&mode);
+    }
+    if (!g_read_page || g_read_used == ~uint64_t(0)) return nullptr;
+    const int k = __builtin_ctzll(~g_read_used);
+    g_read_used |= uint64_t(1) << k;
+    return g_read_page + k;
+}
+
+void give_slot(ReadSlot* slot) {
+    std::lock_guard<std::mutex> lock(g_read_mu);
+    g_read_used &= ~(uint64_t(1) << (slot - g_read_page));
+}
+
+// words (at most kReadWords) 8-byte words at src, as of the end of the work
+// enqueued on the stream.  Not under capture.
+int read_back(const void* src, uint64_t* dst, int words, hipStream_t s) {
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) {
+        (void)hipGetLastError();
+        return LINPRIM_ERR_HIP;
+    }
+    if (ReadSlot* slot = take_slot()) {
+        const uint64_t seq = g_read_seq.fetch_add(1);
+        hipLaunchKernelGGL(k_read_back, dim3(1), dim3(64), 0, s, static_cast<const uint64_t*>(src), words, slot, seq);
+        if (hipGetLastError() == hipSuccess) {
+            const auto t0 = std::chrono::steady_clock::now();
+            bool here = false;
+            while (!(here = __atomic_load_n(&slot->seq, __ATOMIC_ACQUIRE) == seq)) {
+                if (std::chrono::steady_clock::now() - t0 > std::chrono::microseconds(kPollMicros)) break;
+                __builtin_ia32_pause();
+            }
+            // a slot that a failed stream may still write to is not used again
+            if (!here && hipStreamSynchronize(s) != hipSuccess) return LINPRIM_ERR_HIP;
+            here = here || __atomic_load_n(&slot->seq, __ATOMIC_ACQUIRE) == seq;
+            if (here)
+                for (int k = 0; k < words; ++k) dst[k] = __atomic_load_n(&slot->word[k], __ATOMIC_RELAXED);
+            give_slot(slot);
+            if (here) return LINPRIM_OK;
+        } else {
+            give_slot(slot);
+        }
+    }
+    if (hipMemcpyAsync(dst, src, sizeof(uint64_t) * (size_t)words, hipMemcpyDeviceToHost, s) != hipSuccess ||
+        hipStreamSynchronize(s) != hipSuccess)
+        return LINPRIM_ERR_HIP;
+    return LINPRIM_OK;
+}
 
 bool valid_tile(int t) { return t == 8 || t == 16 || t == 32; }
 
@@ -199,11 +298,10 @@ int linprim_upload_views(const linprim_camera* cams, int32_t n_views, const linp
 
 int linprim_pair_count(const void* view_ws, int64_t* n_pairs, void* stream) {
     if (!view_ws || !n_pairs) return LINPRIM_ERR_INVALID_ARG;
-    Status st;
-    hipStream_t s = (hipStream_t)stream;
-    if (hipMemcpyAsync(&st, view_ws, sizeof(Status), hipMemcpyDeviceToHost, s) != hipSuccess) return LINPRIM_ERR_HIP;
-    if (hipStreamSynchronize(s) != hipSuccess) return LINPRIM_ERR_HIP;
-    *n_pairs = (int64_t)st.n_pairs;
+    static_assert(offsetof(Status, n_pairs) == 0 && offsetof(Status, overflow) == 8, "the status's first two words");
+    uint64_t st;
+    if (int rc = read_back(view_ws, &st, 1, (hipStream_t)stream)) return rc;
+    *n_pairs = (int64_t)st;
     return LINPRIM_OK;
 }
 
@@ -376,10 +474,9 @@ int linprim_densify_plan(int32_t type, int64_t n, const float* dists, const floa
                                        densify_params(params), params->extent, bs, s);
     if (e != hipSuccess) return LINPRIM_ERR_HIP;
     const int64_t nb = (n + kDensifyItems - 1) / kDensifyItems;
-    int64_t total = 0;
-    if (hipMemcpyAsync(&total, bs + nb, sizeof(int64_t), hipMemcpyDeviceToHost, s) != hipSuccess) return LINPRIM_ERR_HIP;
-    if (hipStreamSynchronize(s) != hipSuccess) return LINPRIM_ERR_HIP;
-    *n_out = total;
+    uint64_t total = 0;
+    if (int rc = read_back(bs + nb, &total, 1, s)) return rc;
+    *n_out = (int64_t)total;
     return LINPRIM_OK;
 }
 
@@ -438,12 +535,10 @@ int linprim_densify_noalloc(int32_t type, int32_t sh_degree, int64_t n, const li
                             densify_params(params), params->extent, bs, s) != hipSuccess)
         return LINPRIM_ERR_HIP;
     const int64_t nb = (n + kDensifyItems - 1) / kDensifyItems;
-    int64_t total = 0;
-    if (hipMemcpyAsync(&total, bs + nb, sizeof(int64_t), hipMemcpyDeviceToHost, s) != hipSuccess ||
-        hipStreamSynchronize(s) != hipSuccess)
-        return LINPRIM_ERR_HIP;
-    *n_out = total;
-    if (total > dst_rows) return LINPRIM_ERR_WORKSPACE;
+    uint64_t total = 0;
+    if (int rc = read_back(bs + nb, &total, 1, s)) return rc;
+    *n_out = (int64_t)total;
+    if (*n_out > dst_rows) return LINPRIM_ERR_WORKSPACE;
     return hip_status(launch_densify_apply(type, sh_degree, n, state_set(src), normals, grad_accum, count,
                                            max_radius, densify_params(params), params->extent, bs, state_set(dst),
                                            s));
@@ -482,12 +577,9 @@ int linprim_mcmc_dead_count(const void* ws, size_t ws_bytes, int64_t n, int64_t*
         *n_dead = 0;
         return LINPRIM_OK;
     }
-    hipStream_t s = (hipStream_t)stream;
-    int64_t v = 0;
-    if (hipMemcpyAsync(&v, (const char*)ws + mc_dead_offset(n), 8, hipMemcpyDeviceToHost, s) != hipSuccess ||
-        hipStreamSynchronize(s) != hipSuccess)
-        return LINPRIM_ERR_HIP;
-    *n_dead = v;
+    uint64_t v = 0;
+    if (int rc = read_back((const char*)ws + mc_dead_offset(n), &v, 1, (hipStream_t)stream)) return rc;
+    *n_dead = (int64_t)v;
     return LINPRIM_OK;
 }
 
@@ -640,12 +732,10 @@ int linprim_step_guard(const linprim_prims* prims, const linprim_camera* cams, i
 
 int linprim_read_status(const void* view_ws, int64_t* pairs_needed, int32_t* overflow, void* stream) {
     if (!view_ws || !pairs_needed || !overflow) return LINPRIM_ERR_INVALID_ARG;
-    Status st;
-    hipStream_t s = (hipStream_t)stream;
-    if (hipMemcpyAsync(&st, view_ws, sizeof(Status), hipMemcpyDeviceToHost, s) != hipSuccess) return LINPRIM_ERR_HIP;
-    if (hipStreamSynchronize(s) != hipSuccess) return LINPRIM_ERR_HIP;
-    *pairs_needed = (int64_t)st.n_pairs;
-    *overflow = (int32_t)st.overflow;
+    uint64_t st[2];   // n_pairs; overflow in the low half of the second word
+    if (int rc = read_back(view_ws, st, 2, (hipStream_t)stream)) return rc;
+    *pairs_needed = (int64_t)st[0];
+    *overflow = (int32_t)(uint32_t)st[1];
     return LINPRIM_OK;
 }
 

@@ -180,7 +180,9 @@ def _ptr(t: Optional[torch.Tensor]):
 
 def _stream(stream=None):
     if stream is None:
-        stream = torch.cuda.current_stream()
+        # torch.cuda.current_stream().cuda_stream without building the Stream
+        # object (0.2 us instead of 3.1, six times a training step)
+        return ctypes.c_void_p(torch._C._cuda_getCurrentRawStream(torch.cuda.current_device()))
     return ctypes.c_void_p(stream.cuda_stream)
 
 
