@@ -740,12 +740,12 @@ __device__ inline bool bwd_step(const Rec& R, bool active, float pxf, float pyf,
 #pragma unroll
         for (int s = 0; s < 4; ++s) {
             const float gh = eh[s] ? gD : 0.0f;
-            const float gl = el[s] ? gD : 0.0f;
-            const float d = gh - gl;
+            const float gl = el[s] ? -gD : 0.0f;
+            const float d = gh + gl;
             acc[4 * s + 0] = d * ki;
             acc[4 * s + 1] = d * kj;
             acc[4 * s + 2] = gh;
-            acc[4 * s + 3] = gl;                   // negated after the reduction
+            acc[4 * s + 3] = gl;
         }
     } else {
         const int fh = (R.fmap >> (2 * ih)) & 3;
@@ -819,6 +819,8 @@ __global__ __launch_bounds__(64) void k_render_bwd(const ViewInfo* __restrict__ 
         }
     }
 
+    const int ridx = reduce20_index(lane);   // the word of a record this lane writes
+    uint32_t word = 4u * (uint32_t)ridx;
     for (uint32_t e_hi = walk_end; e_hi > rg.x;) {
         const uint32_t nb = min(64u, e_hi - rg.x);
         const uint32_t e0 = e_hi - nb;
@@ -843,10 +845,10 @@ __global__ __launch_bounds__(64) void k_render_bwd(const ViewInfo* __restrict__ 
             const size_t slot = (uint32_t)__builtin_amdgcn_readlane((int)bt.off, bcur);
             float outv = 0.0f;
             if (__ballot(contributed) != 0) outv = wave_reduce20(acc, lane);
-            const int ridx = reduce20_index(lane);
-            // octahedra: words 4 s + 3 are dL/dDlo = -sum of the lower-plane terms
-            if (!EXACT && KIND == LINPRIM_OCTAHEDRON && ridx < 16 && (ridx & 3) == 3) outv = -outv;
-            if (ridx >= 0) grads[slot * kGradWords + ridx] = outv;
+            // a scalar address and the lane's offset, kept apart: a 64-bit
+            // multiply-add per lane costs four issue slots
+            asm("" : "+v"(word));
+            if (ridx >= 0) *reinterpret_cast<float*>(reinterpret_cast<char*>(grads + slot * kGradWords) + word) = outv;
         };
         Rec RA, RB;
         int bA = next_rec(RA), bB = 0;
@@ -1078,17 +1080,12 @@ __global__ __launch_bounds__(64) void k_render_bwd_rows(const ViewInfo* __restri
                 }
             }
         }
-        // the batch's records, one per lane (octahedra: words 4 s + 3 are
-        // dL/dDlo = -sum of the lower-plane terms)
+        // the batch's records, one per lane
         if (meets) {
             const float4* acc4 = reinterpret_cast<const float4*>(sacc[lane]);
             float4* dst = reinterpret_cast<float4*>(grads + (size_t)off * kGradWords);
 #pragma unroll
-            for (int k = 0; k < kGradWords / 4; ++k) {
-                float4 o = acc4[k];
-                if (!EXACT && KIND == LINPRIM_OCTAHEDRON && k < 4) o.w = -o.w;
-                dst[k] = o;
-            }
+            for (int k = 0; k < kGradWords / 4; ++k) dst[k] = acc4[k];
         }
     }
 }

@@ -312,29 +312,32 @@ __device__ inline float wave_reduce20(const float (&v)[20], int lane) {
         const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v[j]), __float_as_uint(v[j + 10]), false, false);
         a[j] = __uint_as_float(r[0]) + __uint_as_float(r[1]);
     }
-    float b[6];
+    float b[5];
 #pragma unroll
     for (int j = 0; j < 5; ++j) {
         const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(a[j]), __float_as_uint(a[j + 5]), false, false);
         b[j] = __uint_as_float(r[0]) + __uint_as_float(r[1]);
     }
-    b[5] = 0.0f;
-    const bool h3 = (lane >> 3) & 1, h2 = (lane >> 2) & 1, h1 = (lane >> 1) & 1;
-    float c[4];
-#pragma unroll
-    for (int p = 0; p < 3; ++p) {                       // lanes i and 15 - i
-        const float keep = h3 ? b[2 * p + 1] : b[2 * p];
-        const float give = h3 ? b[2 * p] : b[2 * p + 1];
-        c[p] = keep + dpp_mov<0x140>(give);
-    }
-    c[3] = 0.0f;
-    float d[2];
-#pragma unroll
-    for (int q = 0; q < 2; ++q) {                       // lanes i and 7 - i of a half row
-        const float keep = h2 ? c[2 * q + 1] : c[2 * q];
-        const float give = h2 ? c[2 * q] : c[2 * q + 1];
-        d[q] = keep + dpp_mov<0x141>(give);
-    }
+    // Where the halves of a row or half row keep different values, each half's
+    // banks take their own pair's sum: one add writes all lanes, the next one
+    // the other half (bank masks), in place of two selects and an add (8 VALU
+    // instructions of the backward walk's 116 per entry; 16 views of 500k
+    // octahedra: k_render_bwd 1170 -> 1110 us, with the record's scalar store
+    // address).  The lanes of v >= 5 hold sums nobody reads.  Reading a
+    // register through DPP takes two wait states after its write.
+    const bool h1 = (lane >> 1) & 1;
+    float c[3], d[2];
+    asm("s_nop 1\n\t"
+        "v_add_f32_dpp %0, %5, %5 row_mirror row_mask:0xf bank_mask:0xf\n\t"        // lanes i and 15 - i
+        "v_add_f32_dpp %1, %7, %7 row_mirror row_mask:0xf bank_mask:0xf\n\t"
+        "v_add_f32_dpp %2, %9, %9 row_mirror row_mask:0xf bank_mask:0xf\n\t"
+        "v_add_f32_dpp %0, %6, %6 row_mirror row_mask:0xf bank_mask:0xc\n\t"
+        "v_add_f32_dpp %1, %8, %8 row_mirror row_mask:0xf bank_mask:0xc\n\t"
+        "v_add_f32_dpp %4, %2, %2 row_half_mirror row_mask:0xf bank_mask:0xf\n\t"   // lanes i and 7 - i
+        "v_add_f32_dpp %3, %0, %0 row_half_mirror row_mask:0xf bank_mask:0xf\n\t"
+        "v_add_f32_dpp %3, %1, %1 row_half_mirror row_mask:0xf bank_mask:0xa"
+        : "=&v"(c[0]), "=&v"(c[1]), "=&v"(c[2]), "=&v"(d[0]), "=&v"(d[1])
+        : "v"(b[0]), "v"(b[1]), "v"(b[2]), "v"(b[3]), "v"(b[4]));
     const float keep = h1 ? d[1] : d[0];               // lanes i and i ^ 2
     const float give = h1 ? d[0] : d[1];
     float e = keep + dpp_mov<0x4E>(give);
