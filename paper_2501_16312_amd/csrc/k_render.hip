@@ -3,14 +3,16 @@
 //
 // Work decomposition (gfx950, wave64):
 //   * one 64-lane wavefront per 8 x 8 pixel group; a TILE x TILE screen tile
-//     has (TILE/8)^2 groups, each an independent workgroup; lane l owns pixel
-//     (l & 7, l >> 3) of its group;
-//   * the tile's sorted list is walked in batches of 64 entries: one vector
-//     load brings 64 primitive indices (and, for tiles wider than a group,
-//     their pixel rectangles), a ballot keeps the entries whose rectangle
-//     meets the group, and only those entries' 32-dword payloads are read,
-//     wave-uniform, through scalar loads issued one entry ahead (no LDS, no
-//     barriers);
+//     has (TILE/8)^2 groups, each an independent workgroup; a lane owns one
+//     pixel of its group;
+//   * forward: the list is taken 32 entries at a time with their records
+//     staged in LDS, and each 16-lane row of the wave walks the entries whose
+//     rectangle meets its 4 x 4 quad of the group;
+//   * backward: batches of 64 entries, one vector load brings 64 primitive
+//     indices and their pixel rectangles, a ballot keeps the entries whose
+//     rectangle meets the group, and only those entries' 32-dword payloads are
+//     read, wave-uniform, through scalar loads issued one entry ahead (no LDS,
+//     no barriers), so that an entry's gradients are summed by the whole wave;
 //   * a pixel is evaluated only inside the primitive's pixel rectangle, so
 //     images do not depend on the tile size.
 //
@@ -88,23 +90,14 @@ __device__ inline int find_view(const ViewInfo* __restrict__ views, int n_views,
 // kernels evaluate bit-identical chords; fused multiply-adds are explicit.
 // ---------------------------------------------------------------------------
 struct Rec {
-    int i0, j0, i1, j1;
     float s2, r, g, b, fi0, fj0, fwi, fwj;
     float p[18];
     float sigma;
     int fmap;
 };
 
-template <int KIND, bool EXACT = false, bool RECT = true>
+template <int KIND, bool EXACT>
 __device__ inline void load_rec(const float* __restrict__ rec, Rec& R) {
-    if (RECT) {
-        R.i0 = __float_as_int(rec[R_I0]);
-        R.j0 = __float_as_int(rec[R_J0]);
-        R.i1 = __float_as_int(rec[R_I1]);
-        R.j1 = __float_as_int(rec[R_J1]);
-    } else {
-        R.i0 = R.j0 = R.i1 = R.j1 = 0;
-    }
     R.s2 = rec[R_S2];
     R.r = rec[R_RGB];
     R.g = rec[R_RGB + 1];
@@ -120,36 +113,17 @@ __device__ inline void load_rec(const float* __restrict__ rec, Rec& R) {
     R.fmap = (EXACT || KIND == LINPRIM_OCTAHEDRON) ? 0 : __float_as_int(rec[R_FACEMAP]);
 }
 
-// The record words 4.. of an entry staged in LDS, as 16-byte quads.
+// An entry's record words 4.. as a 16-lane row holds them: lane l has words
+// 2 l and 2 l + 1, and an instruction takes one as its DPP operand
+// (row_newbcast), so a record costs two registers and one LDS read.
 template <int KIND, bool EXACT>
 constexpr int rec_quads() {
     return (EXACT || KIND == LINPRIM_OCTAHEDRON) ? 6 : 7;
 }
-template <int KIND, bool EXACT>
-__device__ inline void load_rec_lds(const float4* q, Rec& R) {
-    constexpr int NQD = rec_quads<KIND, EXACT>();
-    float w[4 * NQD];
-#pragma unroll
-    for (int k = 0; k < NQD; ++k) {
-        const float4 v = q[k];
-        w[4 * k] = v.x;
-        w[4 * k + 1] = v.y;
-        w[4 * k + 2] = v.z;
-        w[4 * k + 3] = v.w;
-    }
-    R.s2 = w[0];
-    R.r = w[1];
-    R.g = w[2];
-    R.b = w[3];
-    R.fi0 = w[4];
-    R.fj0 = w[5];
-    R.fwi = w[6];
-    R.fwj = w[7];
-    constexpr int NP = (EXACT || KIND == LINPRIM_OCTAHEDRON) ? 16 : 18;
-#pragma unroll
-    for (int k = 0; k < NP; ++k) R.p[k] = w[8 + k];
+template <int W>
+__device__ inline float row_word(float2 r) {
+    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int((W & 1) ? r.y : r.x), 0x150 + (W >> 1), 0xF, 0xF, true));
 }
-
 // Returns hi - lo; ih / il are the active upper / lower slot (first on ties).
 template <int KIND>
 __device__ inline float chord(const Rec& R, float ki, float kj, int& ih, int& il) {
@@ -186,60 +160,62 @@ __device__ inline float chord(const Rec& R, float ki, float kj, int& ih, int& il
     }
 }
 
-// Same chord without slot tracking (forward).
+// Same chord without slot tracking (forward), from a record spread over the
+// row; lo is the entry depth relative to the centre's ray-space depth.  Each
+// word is taken where it is used: the compiler folds a broadcast into the
+// instruction that reads it only a few instructions away.
+// Broadcasts into multiply-adds are written out (the compiler leaves a move
+// for each), several to a block: a register is read through DPP two wait
+// states after a vector instruction wrote it.
+#define LP_FMAC_ROW(acc, word, lane, x) "v_fmac_f32_dpp " acc ", " word ", " x " row_newbcast:" lane " row_mask:0xf bank_mask:0xf\n\t"
 template <int KIND>
-__device__ inline float chord_fast(const Rec& R, float ki, float kj) {
+__device__ inline float chord_row(float2 r, float ki, float kj, float& lo) {
 #pragma clang fp contract(off)
     if (KIND == LINPRIM_OCTAHEDRON) {
-        float h[4], l[4];
-#pragma unroll
-        for (int s = 0; s < 4; ++s) {
-            const float u = __builtin_fmaf(R.p[4 * s + 0], ki, R.p[4 * s + 1] * kj);
-            h[s] = u + R.p[4 * s + 2];
-            l[s] = u + R.p[4 * s + 3];
-        }
-        const float hi = fminf(fminf(h[0], h[1]), fminf(h[2], h[3]));
-        const float lo = fmaxf(fmaxf(l[0], l[1]), fmaxf(l[2], l[3]));
-        return hi - lo;
+        float u0 = row_word<9>(r) * kj, u1 = row_word<13>(r) * kj, u2 = row_word<17>(r) * kj, u3 = row_word<21>(r) * kj;
+        asm("s_nop 1\n\t"
+            LP_FMAC_ROW("%0", "%4", "4", "%5")
+            LP_FMAC_ROW("%1", "%4", "6", "%5")
+            LP_FMAC_ROW("%2", "%4", "8", "%5")
+            LP_FMAC_ROW("%3", "%4", "10", "%5")
+            : "+v"(u0), "+v"(u1), "+v"(u2), "+v"(u3)
+            : "v"(r.x), "v"(ki));
+        const float h0 = u0 + row_word<10>(r), l0 = u0 + row_word<11>(r);
+        const float h1 = u1 + row_word<14>(r), l1 = u1 + row_word<15>(r);
+        const float h2 = u2 + row_word<18>(r), l2 = u2 + row_word<19>(r);
+        const float h3 = u3 + row_word<22>(r), l3 = u3 + row_word<23>(r);
+        lo = fmaxf(fmaxf(l0, l1), fmaxf(l2, l3));
+        return fminf(fminf(h0, h1), fminf(h2, h3)) - lo;
     } else {
-        float h[3], l[3];
-#pragma unroll
-        for (int s = 0; s < 3; ++s) {
-            h[s] = __builtin_fmaf(R.p[3 * s + 0], ki, __builtin_fmaf(R.p[3 * s + 1], kj, R.p[3 * s + 2]));
-            l[s] = __builtin_fmaf(R.p[9 + 3 * s + 0], ki, __builtin_fmaf(R.p[9 + 3 * s + 1], kj, R.p[9 + 3 * s + 2]));
-        }
-        return fminf(fminf(h[0], h[1]), h[2]) - fmaxf(fmaxf(l[0], l[1]), l[2]);
+        float h0 = row_word<10>(r), h1 = row_word<13>(r), h2 = row_word<16>(r);
+        float l0 = row_word<19>(r), l1 = row_word<22>(r), l2 = row_word<25>(r);
+        asm("s_nop 1\n\t"
+            LP_FMAC_ROW("%0", "%7", "4", "%9")
+            LP_FMAC_ROW("%1", "%6", "6", "%9")
+            LP_FMAC_ROW("%2", "%7", "7", "%9")
+            LP_FMAC_ROW("%3", "%6", "9", "%9")
+            LP_FMAC_ROW("%4", "%7", "10", "%9")
+            LP_FMAC_ROW("%5", "%6", "12", "%9")
+            LP_FMAC_ROW("%0", "%6", "4", "%8")
+            LP_FMAC_ROW("%1", "%7", "5", "%8")
+            LP_FMAC_ROW("%2", "%6", "7", "%8")
+            LP_FMAC_ROW("%3", "%7", "8", "%8")
+            LP_FMAC_ROW("%4", "%6", "10", "%8")
+            LP_FMAC_ROW("%5", "%7", "11", "%8")
+            : "+v"(h0), "+v"(h1), "+v"(h2), "+v"(l0), "+v"(l1), "+v"(l2)
+            : "v"(r.x), "v"(r.y), "v"(ki), "v"(kj));
+        lo = fmaxf(fmaxf(l0, l1), l2);
+        return fminf(fminf(h0, h1), h2) - lo;
     }
 }
-
-// Same chord, also returning the entry depth lo (relative to the centre's
-// ray-space depth) for the depth map.
-template <int KIND>
-__device__ inline float chord_entry(const Rec& R, float ki, float kj, float& lo_out) {
-#pragma clang fp contract(off)
-    if (KIND == LINPRIM_OCTAHEDRON) {
-        float h[4], l[4];
-#pragma unroll
-        for (int s = 0; s < 4; ++s) {
-            const float u = __builtin_fmaf(R.p[4 * s + 0], ki, R.p[4 * s + 1] * kj);
-            h[s] = u + R.p[4 * s + 2];
-            l[s] = u + R.p[4 * s + 3];
-        }
-        const float hi = fminf(fminf(h[0], h[1]), fminf(h[2], h[3]));
-        const float lo = fmaxf(fmaxf(l[0], l[1]), fmaxf(l[2], l[3]));
-        lo_out = lo;
-        return hi - lo;
-    } else {
-        float h[3], l[3];
-#pragma unroll
-        for (int s = 0; s < 3; ++s) {
-            h[s] = __builtin_fmaf(R.p[3 * s + 0], ki, __builtin_fmaf(R.p[3 * s + 1], kj, R.p[3 * s + 2]));
-            l[s] = __builtin_fmaf(R.p[9 + 3 * s + 0], ki, __builtin_fmaf(R.p[9 + 3 * s + 1], kj, R.p[9 + 3 * s + 2]));
-        }
-        const float lo = fmaxf(fmaxf(l[0], l[1]), l[2]);
-        lo_out = lo;
-        return fminf(fminf(h[0], h[1]), h[2]) - lo;
-    }
+// c += w rgb
+__device__ inline void add_colour_row(float2 r, float w, float& c0, float& c1, float& c2) {
+    asm("s_nop 1\n\t"
+        LP_FMAC_ROW("%0", "%4", "0", "%5")
+        LP_FMAC_ROW("%1", "%3", "1", "%5")
+        LP_FMAC_ROW("%2", "%4", "1", "%5")
+        : "+v"(c0), "+v"(c1), "+v"(c2)
+        : "v"(r.x), "v"(r.y), "v"(w));
 }
 
 // Exact variant (no ray space): each plane k bounds the relative depth tau
@@ -253,33 +229,63 @@ struct ExactPlanes {
     float U, L;
 };
 
+// Plane k with u at the pixel and constant c.
+template <int KIND>
+__device__ inline void exact_plane(float u, float c, int k, ExactPlanes& X) {
+#pragma clang fp contract(off)
+    const float den = c - u;
+    const float inv = __builtin_amdgcn_rcpf(den);
+    X.u[k] = u;
+    X.inv[k] = inv;
+    if (KIND == LINPRIM_OCTAHEDRON) {
+        const float ui = u * inv;
+        const float t1 = ui - inv, t2 = ui + inv;
+        X.hi[k] = fmaxf(t1, t2);
+        X.lo[k] = fminf(t1, t2);
+    } else {
+        const float t = __builtin_fmaf(u, inv, inv);
+        const bool ex = den >= 0.0f;
+        X.hi[k] = ex ? t : INFINITY;
+        X.lo[k] = ex ? -INFINITY : t;
+    }
+    X.U = fminf(X.U, X.hi[k]);
+    X.L = fmaxf(X.L, X.lo[k]);
+}
+
 template <int KIND>
 __device__ inline void exact_planes(const Rec& R, float ki, float kj, ExactPlanes& X) {
 #pragma clang fp contract(off)
     X.U = INFINITY;
     X.L = -INFINITY;
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        const float u = __builtin_fmaf(R.p[4 * k + 0], ki, __builtin_fmaf(R.p[4 * k + 1], kj, R.p[4 * k + 2]));
-        const float den = R.p[4 * k + 3] - u;
-        const float inv = __builtin_amdgcn_rcpf(den);
-        X.u[k] = u;
-        X.inv[k] = inv;
-        if (KIND == LINPRIM_OCTAHEDRON) {
-            const float ui = u * inv;
-            const float t1 = ui - inv, t2 = ui + inv;
-            X.hi[k] = fmaxf(t1, t2);
-            X.lo[k] = fminf(t1, t2);
-        } else {
-            const float t = __builtin_fmaf(u, inv, inv);
-            const bool ex = den >= 0.0f;
-            X.hi[k] = ex ? t : INFINITY;
-            X.lo[k] = ex ? -INFINITY : t;
-        }
-        X.U = fminf(X.U, X.hi[k]);
-        X.L = fmaxf(X.L, X.lo[k]);
-    }
+    for (int k = 0; k < 4; ++k)
+        exact_plane<KIND>(__builtin_fmaf(R.p[4 * k + 0], ki, __builtin_fmaf(R.p[4 * k + 1], kj, R.p[4 * k + 2])),
+                          R.p[4 * k + 3], k, X);
 }
+
+// The same from a record spread over the row (see chord_row).
+template <int KIND>
+__device__ inline void exact_planes_row(float2 r, float ki, float kj, ExactPlanes& X) {
+    float u0 = row_word<10>(r), u1 = row_word<14>(r), u2 = row_word<18>(r), u3 = row_word<22>(r);
+    asm("s_nop 1\n\t"
+        LP_FMAC_ROW("%0", "%5", "4", "%7")
+        LP_FMAC_ROW("%1", "%5", "6", "%7")
+        LP_FMAC_ROW("%2", "%5", "8", "%7")
+        LP_FMAC_ROW("%3", "%5", "10", "%7")
+        LP_FMAC_ROW("%0", "%4", "4", "%6")
+        LP_FMAC_ROW("%1", "%4", "6", "%6")
+        LP_FMAC_ROW("%2", "%4", "8", "%6")
+        LP_FMAC_ROW("%3", "%4", "10", "%6")
+        : "+v"(u0), "+v"(u1), "+v"(u2), "+v"(u3)
+        : "v"(r.x), "v"(r.y), "v"(ki), "v"(kj));
+    X.U = INFINITY;
+    X.L = -INFINITY;
+    exact_plane<KIND>(u0, row_word<11>(r), 0, X);
+    exact_plane<KIND>(u1, row_word<15>(r), 1, X);
+    exact_plane<KIND>(u2, row_word<19>(r), 2, X);
+    exact_plane<KIND>(u3, row_word<23>(r), 3, X);
+}
+#undef LP_FMAC_ROW
 
 // |D| (min exits - max entries) with rn = |D| of the pixel ray; the z_c
 // factor of the chord is folded into the record's sigma.
@@ -339,13 +345,12 @@ __device__ inline bool rect_meets_group(int4 r, int gx0, int gy0) {
 }
 
 // One batch of up to 64 list entries starting at e0: lane l holds entry
-// e0 + l's primitive index (and, for the backward, the index of the
-// gradient record of that (tile, primitive) pair and this group).
+// e0 + l's primitive index and the index of the gradient record of that
+// (tile, primitive) pair and this group.
 struct Batch {
     uint32_t idx;
-    uint32_t off;      // gradient record index (backward only)
+    uint32_t off;      // gradient record index
     uint64_t mask;     // entries whose pixel rectangle meets the group
-    uint32_t touch;    // words of the entries' records read only to bring them into L2
 };
 
 // Gradient records of a slot are laid out by tile of its tile rectangle
@@ -355,29 +360,21 @@ __device__ inline uint32_t record_index(int4 r, int tile_shift, int tx, int ty, 
     return (prim_offset + (uint32_t)((ty - ty0) * (tx1 - tx0 + 1) + (tx - tx0))) * (uint32_t)NQ + (uint32_t)q;
 }
 
-template <int NQ, bool WANT_OFF>
+template <int NQ>
 __device__ inline Batch load_batch(const float* __restrict__ base, const uint32_t* __restrict__ vals,
                                    const uint32_t* __restrict__ offs, uint32_t e0, uint32_t nb, int gx0, int gy0,
-                                   int tile_shift = 0, int tx = 0, int ty = 0, int q = 0) {
+                                   int tile_shift, int tx, int ty, int q) {
     const int lane = threadIdx.x;
     Batch B;
     B.idx = 0;
     B.off = 0;
-    B.touch = 0;
     bool rel = false;
     if ((uint32_t)lane < nb) {
         B.idx = vals[e0 + lane];
         const float* rp = base + (size_t)B.idx * kRecordWords;
-        if (NQ == 1 && !WANT_OFF) {
-            rel = true;   // every entry of a group-sized tile meets it
-            B.touch = __float_as_uint(rp[0]);
-        } else {
-            const int4 r = *reinterpret_cast<const int4*>(rp);
-            rel = (NQ == 1) || rect_meets_group(r, gx0, gy0);
-            if (WANT_OFF) B.off = record_index(r, tile_shift, tx, ty, offs[B.idx], NQ, q);
-        }
-        // the record's second 64-byte line, for the scalar loads that follow
-        if (rel) B.touch ^= __float_as_uint(rp[16]);
+        const int4 r = *reinterpret_cast<const int4*>(rp);
+        rel = (NQ == 1) || rect_meets_group(r, gx0, gy0);
+        B.off = record_index(r, tile_shift, tx, ty, offs[B.idx], NQ, q);
     }
     B.mask = __ballot(rel);
     return B;
@@ -394,17 +391,21 @@ __device__ inline Batch load_batch(const float* __restrict__ base, const uint32_
 // parameter tau); the centre's depth is added once per pixel afterwards.
 constexpr float kDepthT = 0.5f;
 
-// Long lists set the kernel's end: a wave issues one instruction every four
-// cycles at best, and the scalar walk's bookkeeping, waits for scalar loads
-// and 42 VALU instructions came to 300 ns an entry under full load (170 ns
-// alone).  Lists of more than kStagedList pairs are walked with their records
-// staged in LDS, 32 entries at a time, the next 32 on their way in registers,
-// at a raised wave priority (1M octahedra at 1080p, longest list 499: kernel
-// 126 -> 90 us).  Shorter lists have the chip's other waves to hide behind, and
-// take fewer registers and issue slots with scalar loads (from 64, 96 or 256
-// pairs on: the same within 2 us, and 52 -> 57 us at 64 with 16-pixel tiles).
-constexpr uint32_t kStagedList = 128;
-
+// What bounds the walk is VALU issue, and most of it went to lanes that a
+// primitive does not touch: with 8-pixel tiles an entry hits 3 to 6 of a
+// group's 64 pixels and its rectangle meets 1.3 to 1.8 of its four quads.  So
+// the rows of a wave walk their own quads' entries, each the next one set in
+// its mask of the batch, and a step evaluates up to four entries at once: 0.43
+// to 0.57 steps an entry.  The pixels of a quad still see the list in order,
+// and blend with the same operations.  A record costs a row one 8-byte LDS
+// read a lane, loaded a step ahead; its words reach the arithmetic as DPP
+// broadcasts, not as registers.  Wave-uniform scalar loads, all lanes on the
+// same entry (and LDS records for lists of more than 128): 93 us for 1M
+// octahedra at 1080p, 568 for 16 views of 500k, 992 for 8 views of 3M; now 69,
+// 358 and 570.  Large primitives, whose rectangles meet every quad, gain
+// nothing from the split, and lose nothing: 124 -> 121 us for a depth map of
+// 500k with 2.9 quads an entry at 16-pixel tiles.
+// Wider tiles first filter the list for the group, so that batches are full.
 __device__ inline double centre_depth(const ViewInfo& V, const float* __restrict__ means, uint32_t prim, bool exact) {
     const double x = means[3 * (size_t)prim], y = means[3 * (size_t)prim + 1], z = means[3 * (size_t)prim + 2];
     const double t0 = V.Rw[0] * x + V.Rw[1] * y + V.Rw[2] * z + V.tw[0];
@@ -423,14 +424,15 @@ __global__ __launch_bounds__(64, 6) void k_render_fwd(const ViewInfo* __restrict
                                                    unsigned long long* __restrict__ counters,
                                                    const float* __restrict__ means,
                                                    float* __restrict__ out_depth, const uint32_t* __restrict__ order) {
-    __shared__ float4 srec[36][rec_quads<KIND, EXACT>()];
-    __shared__ uint32_t spos[32];
+    __shared__ float4 srec[33][8];
+    __shared__ uint2 queue[(TILE == 8) ? 1 : 96];   // (primitive, list position) of entries that meet the group
     if (status->n_pairs > capacity) return;
     constexpr int QX = TILE / 8, NQ = QX * QX;
     const Place P = place_wave<TILE>(views, n_views, order);
     if (P.gx0 >= P.W || P.gy0 >= P.H) return;
-    const int lane = threadIdx.x;
-    const int x = P.gx0 + (lane & 7), y = P.gy0 + (lane >> 3);
+    const int lane = threadIdx.x, row = lane >> 4, li = lane & 15;
+    // row r owns the quad (r & 1, r >> 1) of the group
+    const int x = P.gx0 + 4 * (row & 1) + (li & 3), y = P.gy0 + 4 * (row >> 1) + (li >> 2);
     const bool valid = x < P.W && y < P.H;
     const float pxf = (float)x, pyf = (float)y;
     const float rn = EXACT ? ray_norm(views[P.v], x, y) : 1.0f;
@@ -444,27 +446,23 @@ __global__ __launch_bounds__(64, 6) void k_render_fwd(const ViewInfo* __restrict
     uint32_t half = 0xffffffffu;   // list position at which 1 - T first exceeds 0.5
     float half_entry = 0.0f;       // its entry depth relative to its centre
     const float* base = payload + (size_t)P.v * (size_t)n * kRecordWords;
-    bool alive = true;
-    uint32_t sink = 0;   // keeps the L2-warming loads alive; never stored
-    auto blend = [&](const Rec& R, uint32_t e) {
+    uint32_t seen = 0;             // the batch's last blended entry, from 1
+    auto blend = [&](float2 words, uint32_t e) {
         // Branch-free: lanes that do not see the primitive blend with
         // 1 - o = 1 exactly, which leaves C and T unchanged.
-        const float ki = pxf - R.fi0, kj = pyf - R.fj0;
-        // bitwise &: every test is a plain compare, no short-circuit branches
+        const float ki = pxf - row_word<4>(words), kj = pyf - row_word<5>(words);
         // lane masks of single compares combine in scalar registers
-        const uint64_t m_in = __builtin_amdgcn_ballot_w64(fabsf(ki) <= R.fwi) &
-                              __builtin_amdgcn_ballot_w64(fabsf(kj) <= R.fwj) & live;
+        const uint64_t m_in = __builtin_amdgcn_ballot_w64(fabsf(ki) <= row_word<6>(words)) &
+                              __builtin_amdgcn_ballot_w64(fabsf(kj) <= row_word<7>(words)) & live;
         const bool inside = __builtin_amdgcn_inverse_ballot_w64(m_in);
         float dch, entry = 0.0f;
         if (EXACT) {
             ExactPlanes X;
-            exact_planes<KIND>(R, ki, kj, X);
+            exact_planes_row<KIND>(words, ki, kj, X);
             dch = exact_chord(X, rn);
             entry = X.L;
-        } else if (DEPTH) {
-            dch = chord_entry<KIND>(R, ki, kj, entry);
         } else {
-            dch = chord_fast<KIND>(R, ki, kj);
+            dch = chord_row<KIND>(words, ki, kj, entry);
         }
         const uint64_t m_hit = m_in & __builtin_amdgcn_ballot_w64(dch > 0.0f);
         const bool hitp = __builtin_amdgcn_inverse_ballot_w64(m_hit);
@@ -472,123 +470,137 @@ __global__ __launch_bounds__(64, 6) void k_render_fwd(const ViewInfo* __restrict
             ev += inside ? 1u : 0u;
             hit += hitp ? 1u : 0u;
         }
-        const float ex = hitp ? chord_exp(R.s2, dch) : 1.0f;
+        // broadcasts run with every lane: outside the selection
+        const float eh = chord_exp(row_word<0>(words), dch);
+        const float ex = hitp ? eh : 1.0f;
         const float onemo = fmaxf(ex, kOneMinusOMax);
         const float w = T * (1.0f - onemo);
-        C0 = __builtin_fmaf(w, R.r, C0);
-        C1 = __builtin_fmaf(w, R.g, C1);
-        C2 = __builtin_fmaf(w, R.b, C2);
+        add_colour_row(words, w, C0, C1, C2);
         if (DEPTH) {
             const bool cross = T >= kDepthT && T * onemo < kDepthT;
             half = cross ? e : half;
             half_entry = cross ? entry : half_entry;
         }
         T = T * onemo;
-        last = hitp ? (int)e + 1 : last;
+        seen = hitp ? e + 1 : seen;
         // T only falls where the primitive was hit
         const uint64_t stop = __builtin_amdgcn_ballot_w64(T <= kTStop) & m_hit;
         if (COUNT) term = __builtin_amdgcn_inverse_ballot_w64(stop) ? e + 1 : term;
         live &= ~stop;
-        return live != 0;
     };
-    if (rg.y - rg.x > kStagedList) {
-        constexpr int NQD = rec_quads<KIND, EXACT>(), NH = (NQD + 1) / 2;
-        __builtin_amdgcn_s_setprio(3);
-        const uint32_t sl = (uint32_t)lane & 31u, q0 = ((uint32_t)lane >> 5) * NH;
-        auto left = [&](uint32_t e) { return e < rg.y ? min(32u, rg.y - e) : 0u; };
-        auto index_at = [&](uint32_t e) { return sl < left(e) ? vals[e + sl] : 0u; };
-        // lanes l and l + 32 bring the two halves of entry l's record
-        float4 st[NH];
-        int4 rect1 = make_int4(0, 0, 0, 0);
-        auto fetch = [&](uint32_t idx) {
-            const float4* rp = reinterpret_cast<const float4*>(base + (size_t)idx * kRecordWords);
+    constexpr int NQD = rec_quads<KIND, EXACT>(), NH = (NQD + 1) / 2;
+    const uint32_t sl = (uint32_t)lane & 31u, q0 = ((uint32_t)lane >> 5) * NH;
+    // lanes l and l + 32 bring the two halves of entry l's record
+    float4 st[NH];
+    auto fetch = [&](uint32_t idx) {
+        const float4* rp = reinterpret_cast<const float4*>(base + (size_t)idx * kRecordWords);
 #pragma unroll
-            for (int k = 0; k < NH; ++k) st[k] = rp[1 + min((int)q0 + k, NQD - 1)];
-            if (NQ > 1) rect1 = *reinterpret_cast<const int4*>(rp);
+        for (int k = 0; k < NH; ++k) st[k] = rp[1 + min((int)q0 + k, NQD - 1)];
+    };
+    // entry 32: a record no pixel lies in, for a row without one
+    if (lane < 8) srec[32][lane] = (lane == 1) ? make_float4(0.f, 0.f, -1.f, -1.f) : make_float4(0.f, 0.f, 0.f, 0.f);
+    const float2* words = reinterpret_cast<const float2*>(srec[0]) + li;
+    // The next up to 32 entries that meet the group: their number, their list
+    // positions (lane l: entry l & 31), their records on the way.  A group-sized
+    // tile takes its list as it is; others filter it, 64 entries at a time.
+    constexpr uint32_t CH = (NQ == 1) ? 32 : 64;
+    uint32_t ce = rg.x, qn = 0;
+    auto chunk = [&](uint32_t e) {
+        const uint32_t k = (NQ == 1) ? sl : (uint32_t)lane;
+        return (e < rg.y && k < rg.y - e) ? vals[e + k] : 0u;
+    };
+    uint32_t idx0 = chunk(ce), idx1 = chunk(ce + CH);
+    int4 rect = make_int4(0, 0, 0, 0);
+    if (NQ > 1) rect = *reinterpret_cast<const int4*>(base + (size_t)idx0 * kRecordWords);
+    auto take = [&](uint32_t& pos) {
+        uint32_t n = 0;
+        if (NQ == 1) {
+            n = min(32u, rg.y - ce);
+            pos = ce + sl;
+            if (n) fetch(idx0);
+            ce += n;
+            idx0 = idx1;
+            idx1 = chunk(ce + 32);
+        } else {
+            while (qn < 32 && ce < rg.y) {
+                const bool rel = (uint32_t)lane < rg.y - ce && rect_meets_group(rect, P.gx0, P.gy0);
+                const uint64_t m = __builtin_amdgcn_ballot_w64(rel);
+                const uint32_t r = qn + __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32),
+                                                                  __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+                if (rel) queue[r] = make_uint2(idx0, ce + (uint32_t)lane);
+                qn += (uint32_t)__builtin_popcountll(m);
+                ce += 64;
+                idx0 = idx1;
+                if (ce < rg.y) rect = *reinterpret_cast<const int4*>(base + (size_t)idx0 * kRecordWords);
+                idx1 = chunk(ce + 64);
+            }
+            __builtin_amdgcn_wave_barrier();
+            n = min(32u, qn);
+            const uint2 e = queue[sl < n ? sl : 0u], rest = queue[min(32u + (uint32_t)lane, 95u)];
+            pos = e.y;
+            if (n) fetch(sl < n ? e.x : 0u);
+            qn -= n;
+            __builtin_amdgcn_wave_barrier();
+            if ((uint32_t)lane < qn) queue[lane] = rest;
+        }
+        return n;
+    };
+    uint32_t pos, n_here = take(pos);
+    while (n_here && live) {
+        // which entries' rectangles meet each quad, from the first halves
+        const float4 box = st[1];
+        const float bx0 = box.x - box.z, bx1 = box.x + box.z, by0 = box.y - box.w, by1 = box.y + box.w;
+        const float gx = (float)P.gx0, gy = (float)P.gy0;
+        const uint32_t here = n_here < 32u ? (1u << n_here) - 1u : ~0u;
+        auto meets = [&](float lo, float hi, float q) {
+            return (uint32_t)(__builtin_amdgcn_ballot_w64(lo <= q + 3.0f) & __builtin_amdgcn_ballot_w64(hi >= q));
         };
-        fetch(index_at(rg.x));
-        uint32_t idx1 = index_at(rg.x + 32);
-        for (uint32_t e0 = rg.x; e0 < rg.y && live; e0 += 32) {
-            // the entries that meet the group, one after the other
-            uint32_t mask = left(e0) < 32u ? (1u << left(e0)) - 1u : ~0u;
-            if (NQ > 1) mask &= (uint32_t)__ballot(rect_meets_group(rect1, P.gx0, P.gy0));
-            const int cnt = __builtin_popcount(mask);
-            if ((mask >> sl) & 1u) {
-                const int r = __builtin_popcount(mask & ((1u << sl) - 1u));
+        const uint32_t ml = meets(bx0, bx1, gx) & here, mr = meets(bx0, bx1, gx + 4.0f) & here;
+        const uint32_t mt = meets(by0, by1, gy), mb = meets(by0, by1, gy + 4.0f);
+        const uint32_t mx = (row & 1) ? mr : ml, my = (row & 2) ? mb : mt;
+        uint32_t mask = ((uint32_t)(live >> (lane & 48)) & 0xffffu) ? mx & my : 0u;
 #pragma unroll
-                for (int k = 0; k < NH; ++k)
-                    if ((int)q0 + k < NQD) srec[r][q0 + k] = st[k];
-                if (lane < 32) spos[r] = e0 + sl + 1;
-            }
-            // an odd count is filled up with a record no pixel lies in
-            if (lane < NQD) srec[cnt][lane] = (lane == 1) ? make_float4(0.f, 0.f, -1.f, -1.f) : make_float4(0.f, 0.f, 0.f, 0.f);
-            __builtin_amdgcn_wave_barrier();   // other lanes read what this one staged
-            fetch(idx1);
-            idx1 = index_at(e0 + 64);
-            // inside the batch entries count from 0; their list positions follow after it
-            const int last0 = last;
-            const uint32_t half0 = half, term0 = term;
-            last = 0;
-            half = 0xffffffffu;
-            term = 0;
-            Rec RA, RB;
-            load_rec_lds<KIND, EXACT>(srec[0], RA);
-            load_rec_lds<KIND, EXACT>(srec[1], RB);
-            for (int j = 0; j < cnt && live; j += 2) {
-                // the fences keep each record's loads a whole blend ahead of their use
-                blend(RA, (uint32_t)j);
-                sched_fence();
-                load_rec_lds<KIND, EXACT>(srec[j + 2], RA);
-                sched_fence();
-                blend(RB, (uint32_t)j + 1);
-                sched_fence();
-                load_rec_lds<KIND, EXACT>(srec[j + 3], RB);
-                sched_fence();
-            }
-            last = last ? (int)spos[last - 1] : last0;
-            if (DEPTH) half = (half != 0xffffffffu) ? spos[half] - 1 : half0;
-            if (COUNT) term = term ? spos[term - 1] : term0;
+        for (int k = 0; k < NH; ++k)
+            if ((int)q0 + k < NQD) srec[sl][q0 + k] = st[k];
+        __builtin_amdgcn_wave_barrier();   // other lanes read what this one staged
+        uint32_t pos1;
+        n_here = take(pos1);
+        // inside the batch entries count from 0
+        const uint32_t half0 = half, term0 = term;
+        seen = 0;
+        half = 0xffffffffu;
+        term = 0;
+        auto next = [&](uint32_t& e, float2& w) {
+            e = mask ? (uint32_t)__builtin_ctz(mask) : 32u;
+            mask &= mask - 1u;
+            w = words[e * 16u];
+        };
+        uint32_t eA, eB;
+        float2 wA, wB;
+        next(eA, wA);
+        next(eB, wB);
+        while (live && __builtin_amdgcn_ballot_w64(eA < 32u)) {
+            blend(wA, eA);
+            next(eA, wA);
+            blend(wB, eB);
+            next(eB, wB);
         }
-        __builtin_amdgcn_s_setprio(0);
-    } else {
-        Batch nxt = load_batch<NQ, false>(base, vals, nullptr, rg.x, min(64u, rg.y - rg.x), P.gx0, P.gy0);
-        for (uint32_t e0 = rg.x; e0 < rg.y && alive; e0 += 64) {
-            Batch cur = nxt;
-            const uint32_t e1 = e0 + 64;
-            if (e1 < rg.y) nxt = load_batch<NQ, false>(base, vals, nullptr, e1, min(64u, rg.y - e1), P.gx0, P.gy0);
-            sink ^= cur.touch;
-            uint64_t mask = cur.mask;
-            if (!mask) continue;
-            // Two record buffers used in turn: the next surviving entry's record
-            // is loaded into one while the other is blended, with no copies.
-            auto next_rec = [&](Rec& R) {
-                const int b = __builtin_ctzll(mask);
-                mask &= mask - 1;
-                load_rec<KIND, EXACT>(base + (size_t)(uint32_t)__builtin_amdgcn_readlane((int)cur.idx, b) * kRecordWords, R);
-                return e0 + (uint32_t)b;
-            };
-            // Scalar loads complete out of order, so waiting for one buffer means
-            // waiting for every scalar load in flight: wait first, then issue
-            // the next record's load, then blend from the buffer just waited for.
-            Rec RA, RB;
-            uint32_t eA = next_rec(RA), eB = 0;
-            while (true) {
-                smem_wait_all();
-                const bool haveB = mask != 0;
-                if (haveB) eB = next_rec(RB);
-                sched_fence();
-                if (!blend(RA, eA)) { alive = false; break; }
-                if (!haveB) break;
-                smem_wait_all();
-                const bool haveA = mask != 0;
-                if (haveA) eA = next_rec(RA);
-                sched_fence();
-                if (!blend(RB, eB)) { alive = false; break; }
-                if (!haveA) break;
-            }
+        __builtin_amdgcn_wave_barrier();
+        auto list_pos = [&](uint32_t e) {
+            return (NQ == 1) ? (uint32_t)__builtin_amdgcn_readfirstlane((int)pos) + e : (uint32_t)__shfl((int)pos, (int)(e & 31u));
+        };
+        const uint32_t p_last = list_pos(seen - 1);
+        last = seen ? (int)p_last + 1 : last;
+        if (DEPTH) {
+            const uint32_t p_half = list_pos(half);
+            half = (half != 0xffffffffu) ? p_half : half0;
         }
+        if (COUNT) {
+            const uint32_t p_term = list_pos(term - 1);
+            term = term ? p_term + 1 : term0;
+        }
+        pos = pos1;
     }
-    if (n < 0) out_T[0] = __uint_as_float(sink);   // n >= 0: never taken
     unsigned long long c_it = 0, c_ev = 0, c_hit = 0;
     if (valid) {
         const int64_t p = (int64_t)y * P.W + x;
@@ -808,7 +820,7 @@ __global__ __launch_bounds__(64) void k_render_bwd(const ViewInfo* __restrict__ 
 
     // zero records of the entries that meet the group but no pixel reached
     for (uint32_t e0 = walk_end; e0 < rg.y; e0 += 64) {
-        const Batch bt = load_batch<NQ, true>(base, vals, offs, e0, min(64u, rg.y - e0), P.gx0, P.gy0, SHIFT, P.tx,
+        const Batch bt = load_batch<NQ>(base, vals, offs, e0, min(64u, rg.y - e0), P.gx0, P.gy0, SHIFT, P.tx,
                                               P.ty, P.q);
         uint64_t mask = bt.mask;
         while (mask) {
@@ -825,7 +837,7 @@ __global__ __launch_bounds__(64) void k_render_bwd(const ViewInfo* __restrict__ 
         const uint32_t nb = min(64u, e_hi - rg.x);
         const uint32_t e0 = e_hi - nb;
         e_hi = e0;
-        const Batch bt = load_batch<NQ, true>(base, vals, offs, e0, nb, P.gx0, P.gy0, SHIFT, P.tx, P.ty, P.q);
+        const Batch bt = load_batch<NQ>(base, vals, offs, e0, nb, P.gx0, P.gy0, SHIFT, P.tx, P.ty, P.q);
         uint64_t mask = bt.mask;
         if (!mask) continue;
         // Entries in reverse order, two record buffers used in turn (see the
@@ -833,7 +845,7 @@ __global__ __launch_bounds__(64) void k_render_bwd(const ViewInfo* __restrict__ 
         auto next_rec = [&](Rec& R) {
             const int b = 63 - __builtin_clzll(mask);
             mask &= ~(1ull << b);
-            load_rec<KIND, EXACT, false>(base + (size_t)(uint32_t)__builtin_amdgcn_readlane((int)bt.idx, b) *
+            load_rec<KIND, EXACT>(base + (size_t)(uint32_t)__builtin_amdgcn_readlane((int)bt.idx, b) *
                                              kRecordWords, R);
             return b;
         };
@@ -990,7 +1002,7 @@ __global__ __launch_bounds__(64) void k_render_bwd_rows(const ViewInfo* __restri
 
     // zero records of the entries that meet the group but no pixel reached
     for (uint32_t e0 = walk_end; e0 < rg.y; e0 += 64) {
-        const Batch bt = load_batch<NQ, true>(base, vals, offs, e0, min(64u, rg.y - e0), P.gx0, P.gy0, SHIFT, P.tx,
+        const Batch bt = load_batch<NQ>(base, vals, offs, e0, min(64u, rg.y - e0), P.gx0, P.gy0, SHIFT, P.tx,
                                               P.ty, P.q);
         uint64_t mask = bt.mask;
         while (mask) {
@@ -1061,7 +1073,6 @@ __global__ __launch_bounds__(64) void k_render_bwd_rows(const ViewInfo* __restri
                 for (int k = 0; k < 18; ++k) R.p[k] = pw[k];
                 R.sigma = pw[R_SIGMA - R_PLANES];
                 R.fmap = (EXACT || KIND == LINPRIM_OCTAHEDRON) ? 0 : __float_as_int(pw[R_FACEMAP - R_PLANES]);
-                R.i0 = R.j0 = R.i1 = R.j1 = 0;
             }
             const uint32_t e = e0 + (uint32_t)bcur;
             float acc[kGradWords];

@@ -1,8 +1,9 @@
-"""The forward's two walks of a tile's list (scalar record loads up to 128
-pairs, records staged in LDS 32 at a time beyond) at the lengths where they
-meet and where a batch is full, one over or has an odd rest, vs the FP64
-oracle on the GPU: image, transmittance, last blended position, counters and
-depth map, at the tolerances of the other forward tests."""
+"""The forward's walk of a tile's list (records staged in LDS 32 at a time,
+each 16-lane row walking the entries that meet its 4 x 4 quad; tiles wider
+than a group filter the list 64 entries at a time) at the lengths where a
+batch is full, one over or has an odd rest, vs the FP64 oracle on the GPU:
+image, transmittance, last blended position, counters and depth map, at the
+tolerances of the other forward tests."""
 import numpy as np
 import pytest
 import torch
@@ -15,11 +16,13 @@ OCTA, TETRA = scenes.OCTAHEDRON, scenes.TETRAHEDRON
 
 
 @pytest.mark.parametrize("kind,exact", [(OCTA, False), (OCTA, True), (TETRA, False), (TETRA, True)])
-@pytest.mark.parametrize("n,tile,faint", [(128, 8, True), (129, 8, True), (160, 8, False), (161, 16, True),
+@pytest.mark.parametrize("n,tile,faint", [(1, 8, False), (31, 8, True), (32, 16, False), (33, 8, False),
+                                          (63, 32, True), (64, 16, True), (65, 16, False), (97, 32, False),
+                                          (128, 8, True), (129, 8, True), (160, 8, False), (161, 16, True),
                                           (191, 8, True), (193, 32, True), (400, 16, False)])
-def test_staged_walk(kind, exact, n, tile, faint):
+def test_quad_walk(kind, exact, n, tile, faint):
     import oracle
-    print(f"staged walk kind={kind} exact={exact} n={n} tile={tile} faint={faint}", flush=True)
+    print(f"quad walk kind={kind} exact={exact} n={n} tile={tile} faint={faint}", flush=True)
     gen = scenes.uniform_octahedra if kind == OCTA else scenes.uniform_tetrahedra
     # every primitive lies in the one tile of the image, most of them across
     # only some of its 8 x 8 groups
@@ -34,7 +37,7 @@ def test_staged_walk(kind, exact, n, tile, faint):
     O = oracle.OracleScene(sc, cams, tile=tile, exact=exact)
     r = O.render(bg=np.asarray(bg))
     r["cams"] = cams
-    label = f"staged {kind} {exact} {n} {tile}"
+    label = f"quads {kind} {exact} {n} {tile}"
     GC.compare_images(g, r, label, max_excluded=2e-2)
     GC.compare_last(g, r, label)
     GC.compare_counts(g["counts"], r["counts"], label)
