@@ -404,7 +404,7 @@ constexpr float kDepthT = 0.5f;
 // octahedra at 1080p, 568 for 16 views of 500k, 992 for 8 views of 3M; now 69,
 // 358 and 570.  Large primitives, whose rectangles meet every quad, gain
 // nothing from the split, and lose nothing: 124 -> 121 us for a depth map of
-// 500k with 2.9 quads an entry at 16-pixel tiles.
+// 500k with 2.9 quads an entry at 16-pixel tiles (88 with the outlines' test).
 // Wider tiles first filter the list for the group, so that batches are full.
 __device__ inline double centre_depth(const ViewInfo& V, const float* __restrict__ means, uint32_t prim, bool exact) {
     const double x = means[3 * (size_t)prim], y = means[3 * (size_t)prim + 1], z = means[3 * (size_t)prim + 2];
@@ -413,6 +413,83 @@ __device__ inline double centre_depth(const ViewInfo& V, const float* __restrict
     const double t2 = V.Rw[6] * x + V.Rw[7] * y + V.Rw[8] * z + V.tw[2];
     return exact ? t2 : sqrt(t0 * t0 + t1 * t1 + t2 * t2);
 }
+
+// Whether no pixel centre of a quad can have a chord through the primitive,
+// for the quads at x = qx and qx + 4 and y = qy (bits 0 and 1).  A chord needs
+// every upper plane above every lower one at the pixel; the difference of two
+// planes is linear, so over the part of the quad inside the pixel rectangle it
+// is at most |da| hx + |db| hy above the middle's.  One pair below zero
+// everywhere drops the entry; those lines hold the edges of the primitive's
+// outline.  The margin covers the rounding of both evaluations: at most 6 eps M
+// in a pixel's h - l and 25 eps M here, eps = 2^-24 and M the largest
+// |A| Kx + |B| Ky + |D| of a plane; 64 eps M is taken.  A NaN or an infinite M
+// keeps the entry.
+// Planes are read one pair at a time, in order, to take few registers.
+template <int KIND>
+__device__ inline uint32_t quads_missed(const float* rec, float gx, float gy, float qy) {
+    const float bx = rec[4], by = rec[5], bw = rec[6], bh = rec[7];
+    const float* w = rec + 8;
+    const float kx = fmaxf(fabsf(fmaxf(gx - bx, -bw)), fabsf(fminf(gx + 7.0f - bx, bw)));
+    const float ky = fmaxf(fabsf(fmaxf(gy - by, -bh)), fabsf(fminf(gy + 7.0f - by, bh)));
+    const float y0 = fmaxf(qy - by, -bh), y1 = fminf(qy + 3.0f - by, bh);
+    const float cy = 0.5f * (y0 + y1), hy = 0.5f * (y1 - y0);
+    float cx[2], hx[2], least[2], m = 0.0f;
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+        const float x0 = fmaxf(gx + 4.0f * (float)q - bx, -bw), x1 = fminf(gx + 4.0f * (float)q + 3.0f - bx, bw);
+        cx[q] = 0.5f * (x0 + x1);
+        hx[q] = 0.5f * (x1 - x0);
+        least[q] = INFINITY;
+    }
+    if (KIND == LINPRIM_OCTAHEDRON) {
+#pragma unroll
+        for (int a = 0; a < 4; ++a) {
+            const float p0 = w[4 * a], p1 = w[4 * a + 1], p2 = w[4 * a + 2], p3 = w[4 * a + 3];
+            m = fmaxf(m, __builtin_fmaf(fabsf(p0), kx, __builtin_fmaf(fabsf(p1), ky, fmaxf(fabsf(p2), fabsf(p3)))));
+#pragma unroll
+            for (int b = a + 1; b < 4; ++b) {
+                const float da = p0 - w[4 * b], db = p1 - w[4 * b + 1], up = p2 - w[4 * b + 3], dn = w[4 * b + 2] - p3;
+                const float my = db * cy, ey = fabsf(db) * hy;
+#pragma unroll
+                for (int q = 0; q < 2; ++q) {
+                    const float mid = __builtin_fmaf(da, cx[q], my), ext = __builtin_fmaf(fabsf(da), hx[q], ey);
+                    least[q] = fminf(least[q], fminf((ext + mid) + up, (ext - mid) + dn));
+                }
+                asm volatile("" : "+v"(least[0]), "+v"(least[1]), "+v"(m) : : "memory");
+            }
+        }
+    } else {
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            const float p0 = w[3 * a], p1 = w[3 * a + 1], p2 = w[3 * a + 2];
+            m = fmaxf(m, __builtin_fmaf(fabsf(p0), kx, __builtin_fmaf(fabsf(p1), ky, fabsf(p2))));
+#pragma unroll
+            for (int b = 0; b < 3; ++b) {
+                const float q0 = w[9 + 3 * b], q1 = w[10 + 3 * b], q2 = w[11 + 3 * b];
+                if (a == 0) m = fmaxf(m, __builtin_fmaf(fabsf(q0), kx, __builtin_fmaf(fabsf(q1), ky, fabsf(q2))));
+                const float da = p0 - q0, db = p1 - q1;
+                const float my = __builtin_fmaf(fabsf(db), hy, __builtin_fmaf(db, cy, p2 - q2));
+#pragma unroll
+                for (int q = 0; q < 2; ++q)
+                    least[q] = fminf(least[q], __builtin_fmaf(fabsf(da), hx[q], __builtin_fmaf(da, cx[q], my)));
+                asm volatile("" : "+v"(least[0]), "+v"(least[1]), "+v"(m) : : "memory");
+            }
+        }
+    }
+    const float margin = -0x1p-18f * m;
+    return (least[0] < margin ? 1u : 0u) | (least[1] < margin ? 2u : 0u);
+}
+
+
+// Batches in which some quad's row has at least this many entries test the
+// outlines: the test costs a batch about four steps, and drops a third to a
+// half of the steps where primitives are long and thin (a depth map of 500k
+// octahedra at 16-pixel tiles, 42% of whose entries hit no pixel of the group:
+// kernel 120 -> 88 us; from 16 or 25 on 88 and 94, and 41 -> 43 us from 16 on
+// for a training view whose entries meet 1.8 quads).  8-pixel tiles, whose
+// lists hold smaller rectangles, go without it: the registers it takes cost
+// them more (1M octahedra at 1080p 71 -> 74 us, 16 views of 500k 370 -> 382).
+constexpr int kOutlineSteps = 20;
 
 template <int TILE, int KIND, bool COUNT, bool EXACT, bool DEPTH>
 __global__ __launch_bounds__(64, 6) void k_render_fwd(const ViewInfo* __restrict__ views, int n_views, int64_t n,
@@ -446,6 +523,8 @@ __global__ __launch_bounds__(64, 6) void k_render_fwd(const ViewInfo* __restrict
     uint32_t half = 0xffffffffu;   // list position at which 1 - T first exceeds 0.5
     float half_entry = 0.0f;       // its entry depth relative to its centre
     const float* base = payload + (size_t)P.v * (size_t)n * kRecordWords;
+    // counted renders count every pixel of a rectangle
+    constexpr bool kOutline = NQ > 1 && !EXACT && !COUNT;
     uint32_t seen = 0;             // the batch's last blended entry, from 1
     auto blend = [&](float2 words, uint32_t e) {
         // Branch-free: lanes that do not see the primitive blend with
@@ -557,12 +636,27 @@ __global__ __launch_bounds__(64, 6) void k_render_fwd(const ViewInfo* __restrict
         };
         const uint32_t ml = meets(bx0, bx1, gx) & here, mr = meets(bx0, bx1, gx + 4.0f) & here;
         const uint32_t mt = meets(by0, by1, gy), mb = meets(by0, by1, gy + 4.0f);
-        const uint32_t mx = (row & 1) ? mr : ml, my = (row & 2) ? mb : mt;
-        uint32_t mask = ((uint32_t)(live >> (lane & 48)) & 0xffffu) ? mx & my : 0u;
+        uint32_t m0 = ml & mt, m1 = mr & mt, m2 = ml & mb, m3 = mr & mb;
 #pragma unroll
         for (int k = 0; k < NH; ++k)
             if ((int)q0 + k < NQD) srec[sl][q0 + k] = st[k];
         __builtin_amdgcn_wave_barrier();   // other lanes read what this one staged
+        if (kOutline) {
+            const int steps = max(max(__builtin_popcount(m0), __builtin_popcount(m1)),
+                                  max(__builtin_popcount(m2), __builtin_popcount(m3)));
+            if (steps >= kOutlineSteps) {
+                // lanes l and l + 32 test the upper and the lower quads of entry l
+                const uint32_t missed = quads_missed<KIND>(reinterpret_cast<const float*>(srec[sl]), gx, gy,
+                                                           lane < 32 ? gy : gy + 4.0f);
+                const uint64_t xl = __builtin_amdgcn_ballot_w64(missed & 1u), xr = __builtin_amdgcn_ballot_w64(missed & 2u);
+                m0 &= ~(uint32_t)xl;
+                m1 &= ~(uint32_t)xr;
+                m2 &= ~(uint32_t)(xl >> 32);
+                m3 &= ~(uint32_t)(xr >> 32);
+            }
+        }
+        const uint32_t mine_q = (row & 2) ? ((row & 1) ? m3 : m2) : ((row & 1) ? m1 : m0);
+        uint32_t mask = ((uint32_t)(live >> (lane & 48)) & 0xffffu) ? mine_q : 0u;
         uint32_t pos1;
         n_here = take(pos1);
         // inside the batch entries count from 0
