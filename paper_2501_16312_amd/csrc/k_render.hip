@@ -934,8 +934,10 @@ __global__ __launch_bounds__(64) void k_render_bwd(const ViewInfo* __restrict__ 
         const Batch bt = load_batch<NQ>(base, vals, offs, e0, nb, P.gx0, P.gy0, SHIFT, P.tx, P.ty, P.q);
         uint64_t mask = bt.mask;
         if (!mask) continue;
-        // Entries in reverse order, two record buffers used in turn (see the
-        // forward for the wait / load order).
+        // Entries in reverse order, two record buffers used in turn, with no
+        // copies.  Scalar loads complete out of order, so waiting for one buffer
+        // means waiting for every scalar load in flight: wait first, then issue
+        // the next record's load, then step from the buffer just waited for.
         auto next_rec = [&](Rec& R) {
             const int b = 63 - __builtin_clzll(mask);
             mask &= ~(1ull << b);
