@@ -96,7 +96,7 @@ struct Rec {
     int fmap;
 };
 
-template <int KIND, bool EXACT>
+template <int KIND>
 __device__ inline void load_rec(const float* __restrict__ rec, Rec& R) {
     R.s2 = rec[R_S2];
     R.r = rec[R_RGB];
@@ -106,11 +106,11 @@ __device__ inline void load_rec(const float* __restrict__ rec, Rec& R) {
     R.fj0 = rec[R_FJ0];
     R.fwi = rec[R_FWI];
     R.fwj = rec[R_FWJ];
-    constexpr int NP = (EXACT || KIND == LINPRIM_OCTAHEDRON) ? 16 : 18;
+    constexpr int NP = (KIND == LINPRIM_OCTAHEDRON) ? 16 : 18;
 #pragma unroll
     for (int k = 0; k < NP; ++k) R.p[k] = rec[R_PLANES + k];
     R.sigma = rec[R_SIGMA];
-    R.fmap = (EXACT || KIND == LINPRIM_OCTAHEDRON) ? 0 : __float_as_int(rec[R_FACEMAP]);
+    R.fmap = (KIND == LINPRIM_OCTAHEDRON) ? 0 : __float_as_int(rec[R_FACEMAP]);
 }
 
 // An entry's record words 4.. as a 16-lane row holds them: lane l has words
@@ -747,8 +747,8 @@ __global__ __launch_bounds__(64, 6) void k_render_fwd(const ViewInfo* __restrict
 // leaves T and the colour behind (GB = dL/dC . colour behind) unchanged
 // exactly and yields zero terms.  Writes the lane's gradient terms of the
 // entry's record into acc; returns whether the lane contributed.
-template <int KIND, bool EXACT>
-__device__ inline bool bwd_step(const Rec& R, bool active, float pxf, float pyf, float rn, float G0, float G1,
+template <int KIND>
+__device__ inline bool bwd_step(const Rec& R, bool active, float pxf, float pyf, float G0, float G1,
                                 float G2, float& T, float& GB, float (&acc)[kGradWords]) {
     const float ki = pxf - R.fi0, kj = pyf - R.fj0;
     const bool inside = active & (fabsf(ki) <= R.fwi) & (fabsf(kj) <= R.fwj);
@@ -758,19 +758,7 @@ __device__ inline bool bwd_step(const Rec& R, bool active, float pxf, float pyf,
     float dch;
     bool eh[4], el[4];
     int ih = 0, il = 0;
-    ExactPlanes X;
-    if (EXACT) {
-        exact_planes<KIND>(R, ki, kj, X);
-        dch = exact_chord(X, rn);
-        bool fh = false, fl = false;
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            eh[k] = !fh && X.hi[k] == X.U;
-            el[k] = !fl && X.lo[k] == X.L;
-            fh = fh || eh[k];
-            fl = fl || el[k];
-        }
-    } else if (KIND == LINPRIM_OCTAHEDRON) {
+    if (KIND == LINPRIM_OCTAHEDRON) {
 #pragma clang fp contract(off)
         float h[4], l[4];
 #pragma unroll
@@ -816,33 +804,7 @@ __device__ inline bool bwd_step(const Rec& R, bool active, float pxf, float pyf,
     const float q = dLdo * ex;
     const float gD = open ? q * R.sigma : 0.0f;    // dL/dchord
     acc[19] = open ? q * delta : 0.0f;             // dL/dsigma
-    if (EXACT) {
-        // words 4 k + 0..3: dL/d(a_k, b_k, g_k, c_k); a plane bound
-        // tau = (u + h) / (c - u) has dtau/du = (c + h) / (c - u)^2
-        // and dtau/dc = -tau / (c - u)
-        const float g = gD * rn;                   // dL/d(U - L)
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            const float c = R.p[4 * k + 3];
-            const float inv = X.inv[k];
-            const float ge = eh[k] ? g : 0.0f, gl = el[k] ? g : 0.0f;
-            float gu;
-            if (KIND == LINPRIM_OCTAHEDRON) {
-                // the upper bound has h = +1 where c - u >= 0, else h = -1
-                const float hh = (c - X.u[k] >= 0.0f) ? 1.0f : -1.0f;
-                gu = (ge * (c + hh) - gl * (c - hh)) * (inv * inv);
-            } else {
-                gu = (ge - gl) * (c + 1.0f) * (inv * inv);
-            }
-            const float gc = (gl * X.L - ge * X.U) * inv;
-            const bool act = eh[k] || el[k];
-            const float Gu = act ? gu : 0.0f, Gc = act ? gc : 0.0f;
-            acc[4 * k + 0] = Gu * ki;
-            acc[4 * k + 1] = Gu * kj;
-            acc[4 * k + 2] = Gu;
-            acc[4 * k + 3] = Gc;
-        }
-    } else if (KIND == LINPRIM_OCTAHEDRON) {
+    if (KIND == LINPRIM_OCTAHEDRON) {
 #pragma unroll
         for (int s = 0; s < 4; ++s) {
             const float gh = eh[s] ? gD : 0.0f;
@@ -869,7 +831,78 @@ __device__ inline bool bwd_step(const Rec& R, bool active, float pxf, float pyf,
     return contributed;
 }
 
-template <int TILE, int KIND, bool EXACT>
+// The step of the exact variant, from a record spread over the row.
+template <int KIND>
+__device__ inline bool bwd_step_exact(float2 r, bool active, float pxf, float pyf, float rn, float G0, float G1,
+                                      float G2, float& T, float& GB, float (&acc)[kGradWords]) {
+    const float ki = pxf - row_word<4>(r), kj = pyf - row_word<5>(r);
+    const bool inside = active & (fabsf(ki) <= row_word<6>(r)) & (fabsf(kj) <= row_word<7>(r));
+    ExactPlanes X;
+    exact_planes_row<KIND>(r, ki, kj, X);
+    const float dch = exact_chord(X, rn);
+    bool eh[4], el[4];
+    bool fh = false, fl = false;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        eh[k] = !fh && X.hi[k] == X.U;
+        el[k] = !fl && X.lo[k] == X.L;
+        fh = fh || eh[k];
+        fl = fl || el[k];
+    }
+    // broadcasts run with every lane: outside the selections
+    const float ec = chord_exp(row_word<0>(r), dch);
+    const bool contributed = inside && dch > 0.0f;
+    const float ex = contributed ? ec : 1.0f;
+    const float onemo = fmaxf(ex, kOneMinusOMax);
+    const float o = 1.0f - onemo;
+    const float ro = __builtin_amdgcn_rcpf(onemo);
+    const float Tk = T * ro;                     // transmittance in front of this primitive
+    // dL/do = G . (T_k rgb - behind / (1 - o))
+    const float Grgb = G0 * row_word<1>(r) + G1 * row_word<2>(r) + G2 * row_word<3>(r);
+    const float dLdo = Tk * Grgb - ro * GB;
+    const float wk = Tk * o;
+    acc[16] = G0 * wk;
+    acc[17] = G1 * wk;
+    acc[18] = G2 * wk;
+    GB += wk * Grgb;
+    T = Tk;
+    // not clamped: o = 1 - exp(-sigma chord)
+    const bool open = contributed && ex >= kOneMinusOMax;
+    const float q = dLdo * ex, qs = q * row_word<26>(r);
+    const float gD = open ? qs : 0.0f;             // dL/dchord
+    acc[19] = open ? q * dch : 0.0f;               // dL/dsigma
+    {
+        // words 4 k + 0..3: dL/d(a_k, b_k, g_k, c_k); a plane bound
+        // tau = (u + h) / (c - u) has dtau/du = (c + h) / (c - u)^2
+        // and dtau/dc = -tau / (c - u)
+        const float g = gD * rn;                   // dL/d(U - L)
+        const float cw[4] = {row_word<11>(r), row_word<15>(r), row_word<19>(r), row_word<23>(r)};
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const float c = cw[k];
+            const float inv = X.inv[k];
+            const float ge = eh[k] ? g : 0.0f, gl = el[k] ? g : 0.0f;
+            float gu;
+            if (KIND == LINPRIM_OCTAHEDRON) {
+                // the upper bound has h = +1 where c - u >= 0, else h = -1
+                const float hh = (c - X.u[k] >= 0.0f) ? 1.0f : -1.0f;
+                gu = (ge * (c + hh) - gl * (c - hh)) * (inv * inv);
+            } else {
+                gu = (ge - gl) * (c + 1.0f) * (inv * inv);
+            }
+            const float gc = (gl * X.L - ge * X.U) * inv;
+            const bool act = eh[k] || el[k];
+            const float Gu = act ? gu : 0.0f, Gc = act ? gc : 0.0f;
+            acc[4 * k + 0] = Gu * ki;
+            acc[4 * k + 1] = Gu * kj;
+            acc[4 * k + 2] = Gu;
+            acc[4 * k + 3] = Gc;
+        }
+    }
+    return contributed;
+}
+
+template <int TILE, int KIND>
 __global__ __launch_bounds__(64) void k_render_bwd(const ViewInfo* __restrict__ views, int n_views, int64_t n,
                                                    const float* __restrict__ payload, const uint32_t* __restrict__ vals,
                                                    const uint2* __restrict__ ranges, const uint32_t* __restrict__ offsets,
@@ -887,7 +920,6 @@ __global__ __launch_bounds__(64) void k_render_bwd(const ViewInfo* __restrict__ 
     const int x = P.gx0 + (lane & 7), y = P.gy0 + (lane >> 3);
     const bool valid = x < P.W && y < P.H;
     const float pxf = (float)x, pyf = (float)y;
-    const float rn = EXACT ? ray_norm(views[P.v], x, y) : 1.0f;
     const uint2 rg = ranges[P.g];
     const int64_t hw = (int64_t)P.W * P.H;
     const float* base = payload + (size_t)P.v * (size_t)n * kRecordWords;
@@ -941,7 +973,7 @@ __global__ __launch_bounds__(64) void k_render_bwd(const ViewInfo* __restrict__ 
         auto next_rec = [&](Rec& R) {
             const int b = 63 - __builtin_clzll(mask);
             mask &= ~(1ull << b);
-            load_rec<KIND, EXACT>(base + (size_t)(uint32_t)__builtin_amdgcn_readlane((int)bt.idx, b) *
+            load_rec<KIND>(base + (size_t)(uint32_t)__builtin_amdgcn_readlane((int)bt.idx, b) *
                                              kRecordWords, R);
             return b;
         };
@@ -949,7 +981,7 @@ __global__ __launch_bounds__(64) void k_render_bwd(const ViewInfo* __restrict__ 
             const uint32_t e = e0 + (uint32_t)bcur;
             // a lane past its last blended entry takes no part
             float acc[kGradWords];
-            const bool contributed = bwd_step<KIND, EXACT>(R, (int)e < last, pxf, pyf, rn, G0, G1, G2, T, GB, acc);
+            const bool contributed = bwd_step<KIND>(R, (int)e < last, pxf, pyf, G0, G1, G2, T, GB, acc);
             const size_t slot = (uint32_t)__builtin_amdgcn_readlane((int)bt.off, bcur);
             float outv = 0.0f;
             if (__ballot(contributed) != 0) outv = wave_reduce20(acc, lane);
@@ -984,15 +1016,57 @@ __global__ __launch_bounds__(64) void k_render_bwd(const ViewInfo* __restrict__ 
 // of one of its pixels; the four rows walk independently, so a step
 // evaluates up to four entries.  The list is taken in batches of kBwdBatch
 // entries: the batch's records (words 4..31) are staged in LDS, a row reads
-// the record of its current entry from there, sums its 16 lanes' gradient
+// the record of its current entry from there as the forward does (8 bytes a
+// lane, the words as broadcasts), sums its 16 lanes' gradient
 // terms (transposed, inside the row) and adds them to the entry's LDS
 // accumulator, the rows one after the other (a fixed order); the batch's
 // records are then written out, one per lane.  Same records as
 // k_render_bwd.  The exact step is heavy enough that skipping the entries a
 // quad does not meet pays for the LDS round trips; the ray-space step is not.
+// Bound by VALU issue (85%) and, with whole records read by every lane, by LDS
+// as well (80% of its cycles): 300k octahedra at 1597 x 1199, 144 -> 139 us by
+// the broadcasts, 135 by the bank-masked sums.
 // ---------------------------------------------------------------------------
 constexpr int kBwdBatch = 32;
 static_assert(kBwdBatch <= 32, "entry masks are 32-bit");
+
+// o[j] = x[j] of lanes i and 15 - i (row mirror) or 7 - i (half-row mirror),
+// and y[j] of them in the upper half of the row or half row: an add of all
+// lanes, then one whose bank mask keeps to the upper halves, in place of two
+// selects and an add.
+template <bool ROW>
+__device__ inline void fold5(const float* x, const float* y, float* o) {
+    if (ROW)
+        asm("s_nop 1\n\t"     // a register is read through DPP two wait states after its write
+            "v_add_f32_dpp %0, %5, %5 row_mirror row_mask:0xf bank_mask:0xf\n\t"
+            "v_add_f32_dpp %1, %6, %6 row_mirror row_mask:0xf bank_mask:0xf\n\t"
+            "v_add_f32_dpp %2, %7, %7 row_mirror row_mask:0xf bank_mask:0xf\n\t"
+            "v_add_f32_dpp %3, %8, %8 row_mirror row_mask:0xf bank_mask:0xf\n\t"
+            "v_add_f32_dpp %4, %9, %9 row_mirror row_mask:0xf bank_mask:0xf\n\t"
+            "v_add_f32_dpp %0, %10, %10 row_mirror row_mask:0xf bank_mask:0xc\n\t"
+            "v_add_f32_dpp %1, %11, %11 row_mirror row_mask:0xf bank_mask:0xc\n\t"
+            "v_add_f32_dpp %2, %12, %12 row_mirror row_mask:0xf bank_mask:0xc\n\t"
+            "v_add_f32_dpp %3, %13, %13 row_mirror row_mask:0xf bank_mask:0xc\n\t"
+            "v_add_f32_dpp %4, %14, %14 row_mirror row_mask:0xf bank_mask:0xc"
+            : "=&v"(o[0]), "=&v"(o[1]), "=&v"(o[2]), "=&v"(o[3]), "=&v"(o[4])
+            : "v"(x[0]), "v"(x[1]), "v"(x[2]), "v"(x[3]), "v"(x[4]), "v"(y[0]), "v"(y[1]), "v"(y[2]), "v"(y[3]),
+              "v"(y[4]));
+    else
+        asm("s_nop 1\n\t"
+            "v_add_f32_dpp %0, %5, %5 row_half_mirror row_mask:0xf bank_mask:0xf\n\t"
+            "v_add_f32_dpp %1, %6, %6 row_half_mirror row_mask:0xf bank_mask:0xf\n\t"
+            "v_add_f32_dpp %2, %7, %7 row_half_mirror row_mask:0xf bank_mask:0xf\n\t"
+            "v_add_f32_dpp %3, %8, %8 row_half_mirror row_mask:0xf bank_mask:0xf\n\t"
+            "v_add_f32_dpp %4, %9, %9 row_half_mirror row_mask:0xf bank_mask:0xf\n\t"
+            "v_add_f32_dpp %0, %10, %10 row_half_mirror row_mask:0xf bank_mask:0xa\n\t"
+            "v_add_f32_dpp %1, %11, %11 row_half_mirror row_mask:0xf bank_mask:0xa\n\t"
+            "v_add_f32_dpp %2, %12, %12 row_half_mirror row_mask:0xf bank_mask:0xa\n\t"
+            "v_add_f32_dpp %3, %13, %13 row_half_mirror row_mask:0xf bank_mask:0xa\n\t"
+            "v_add_f32_dpp %4, %14, %14 row_half_mirror row_mask:0xf bank_mask:0xa"
+            : "=&v"(o[0]), "=&v"(o[1]), "=&v"(o[2]), "=&v"(o[3]), "=&v"(o[4])
+            : "v"(x[0]), "v"(x[1]), "v"(x[2]), "v"(x[3]), "v"(x[4]), "v"(y[0]), "v"(y[1]), "v"(y[2]), "v"(y[3]),
+              "v"(y[4]));
+}
 
 // Sums 20 values over the 16 lanes of each row, transposed: four DPP steps
 // each halve the values a lane keeps (row mirror: lane i with 15 - i, split
@@ -1000,49 +1074,33 @@ static_assert(kBwdBatch <= 32, "entry masks are 32-bit");
 // bit 1, and i with i ^ 1, bit 0).  With base = 10 b3 + 5 b2 of the row lane
 // index, a lane ends with the totals of words
 //   b1 b0 = 00: base, base + 1;  01: base + 2;  10: base + 3, base + 4;
-//   11: none.
+//   11: none (such a lane holds sums that nobody reads).
 __device__ inline void row_reduce20(const float (&v)[20], int li, float& t0, float& t1, int& w0, int& w1) {
     const bool h3 = (li >> 3) & 1, h2 = (li >> 2) & 1, h1 = (li >> 1) & 1, h0 = li & 1;
-    float a[10];
+    float a[10], b[5];
+    fold5<true>(v, v + 10, a);
+    fold5<true>(v + 5, v + 15, a + 5);
+    fold5<false>(a, a + 5, b);
+    float c[3];
 #pragma unroll
-    for (int j = 0; j < 10; ++j) {
-        const float keep = h3 ? v[j + 10] : v[j];
-        const float give = h3 ? v[j] : v[j + 10];
-        a[j] = keep + dpp_move<0x140>(give);
-    }
-    float b[6];
-#pragma unroll
-    for (int j = 0; j < 5; ++j) {
-        const float keep = h2 ? a[j + 5] : a[j];
-        const float give = h2 ? a[j] : a[j + 5];
-        b[j] = keep + dpp_move<0x141>(give);
-    }
-    b[5] = 0.0f;
-    float c[4];
-#pragma unroll
-    for (int j = 0; j < 3; ++j) {
+    for (int j = 0; j < 2; ++j) {
         const float keep = h1 ? b[j + 3] : b[j];
         const float give = h1 ? b[j] : b[j + 3];
         c[j] = keep + dpp_move<0x4E>(give);
     }
-    c[3] = 0.0f;
-    float d[2];
-#pragma unroll
-    for (int j = 0; j < 2; ++j) {
-        const float keep = h0 ? c[j + 2] : c[j];
-        const float give = h0 ? c[j] : c[j + 2];
-        d[j] = keep + dpp_move<0xB1>(give);
-    }
+    c[2] = b[2] + dpp_move<0x4E>(b[2]);
+    const float keep = h0 ? c[2] : c[0];
+    const float give = h0 ? c[0] : c[2];
+    t0 = keep + dpp_move<0xB1>(give);
+    t1 = c[1] + dpp_move<0xB1>(c[1]);
     const int base = 10 * (int)h3 + 5 * (int)h2;
-    t0 = d[0];
-    t1 = d[1];
     if (!h1 && !h0) { w0 = base; w1 = base + 1; }
     else if (!h1) { w0 = base + 2; w1 = -1; }
     else if (!h0) { w0 = base + 3; w1 = base + 4; }
     else { w0 = -1; w1 = -1; }
 }
 
-template <int TILE, int KIND, bool EXACT>
+template <int TILE, int KIND>
 __global__ __launch_bounds__(64) void k_render_bwd_rows(const ViewInfo* __restrict__ views, int n_views, int64_t n,
                                                    const float* __restrict__ payload, const uint32_t* __restrict__ vals,
                                                    const uint2* __restrict__ ranges, const uint32_t* __restrict__ offsets,
@@ -1051,7 +1109,7 @@ __global__ __launch_bounds__(64) void k_render_bwd_rows(const ViewInfo* __restri
                                                    const int32_t* __restrict__ out_last,
                                                    const float* __restrict__ grad_rgb, float* __restrict__ grads,
                                                    const uint32_t* __restrict__ order) {
-    __shared__ float4 srec[kBwdBatch][7];             // record words 4..31
+    __shared__ float4 srec[kBwdBatch + 1][8];         // record words 4..31
     __shared__ float sacc[kBwdBatch][kGradWords];     // gradient record accumulators
     if (status->n_pairs > capacity) return;
     constexpr int QX = TILE / 8, NQ = QX * QX;
@@ -1063,7 +1121,7 @@ __global__ __launch_bounds__(64) void k_render_bwd_rows(const ViewInfo* __restri
     const int x = P.gx0 + 4 * (row & 1) + (li & 3), y = P.gy0 + 4 * (row >> 1) + (li >> 2);
     const bool valid = x < P.W && y < P.H;
     const float pxf = (float)x, pyf = (float)y;
-    const float rn = EXACT ? ray_norm(views[P.v], x, y) : 1.0f;
+    const float rn = ray_norm(views[P.v], x, y);
     const uint2 rg = ranges[P.g];
     const int64_t hw = (int64_t)P.W * P.H;
     const float* base = payload + (size_t)P.v * (size_t)n * kRecordWords;
@@ -1109,6 +1167,9 @@ __global__ __launch_bounds__(64) void k_render_bwd_rows(const ViewInfo* __restri
         }
     }
 
+    // the last record: one no pixel lies in, for a row without an entry
+    if (lane < 8) srec[kBwdBatch][lane] = (lane == 1) ? make_float4(0.f, 0.f, -1.f, -1.f) : make_float4(0.f, 0.f, 0.f, 1.f);
+    const float2* words = reinterpret_cast<const float2*>(srec[0]) + li;
     for (uint32_t e_hi = walk_end; e_hi > rg.x;) {
         const uint32_t nb = min((uint32_t)kBwdBatch, e_hi - rg.x);
         const uint32_t e0 = e_hi - nb;
@@ -1141,9 +1202,6 @@ __global__ __launch_bounds__(64) void k_render_bwd_rows(const ViewInfo* __restri
         }
         const uint32_t staged = (uint32_t)__ballot(meets);   // kBwdBatch <= 32 entries
         if (staged == 0) continue;
-        // a staged entry: the record a row without an entry reads (finite
-        // values, so that its lanes' state stays exactly unchanged)
-        const int bsafe = __builtin_ctz(staged);
         const uint32_t m0 = (uint32_t)__ballot(qm & 1u), m1 = (uint32_t)__ballot(qm & 2u),
                        m2 = (uint32_t)__ballot(qm & 4u), m3 = (uint32_t)__ballot(qm & 8u);
         uint32_t mask = (row == 0) ? m0 : (row == 1) ? m1 : (row == 2) ? m2 : m3;
@@ -1152,27 +1210,12 @@ __global__ __launch_bounds__(64) void k_render_bwd_rows(const ViewInfo* __restri
             if (__ballot(act) == 0) break;
             // the row's next entry, in reverse order (a row without one runs
             // the step with every lane outside)
-            const int bcur = act ? 31 - __builtin_clz(mask) : bsafe;
+            const int bcur = act ? 31 - __builtin_clz(mask) : kBwdBatch;
             mask &= act ? ~(1u << bcur) : ~0u;
-            Rec R;
-            {
-                const float4 w0 = srec[bcur][0], w1 = srec[bcur][1];
-                R.s2 = w0.x; R.r = w0.y; R.g = w0.z; R.b = w0.w;
-                R.fi0 = w1.x; R.fj0 = w1.y; R.fwi = w1.z; R.fwj = w1.w;
-                float pw[20];
-#pragma unroll
-                for (int k = 0; k < 5; ++k) {
-                    const float4 w = srec[bcur][2 + k];
-                    pw[4 * k] = w.x; pw[4 * k + 1] = w.y; pw[4 * k + 2] = w.z; pw[4 * k + 3] = w.w;
-                }
-#pragma unroll
-                for (int k = 0; k < 18; ++k) R.p[k] = pw[k];
-                R.sigma = pw[R_SIGMA - R_PLANES];
-                R.fmap = (EXACT || KIND == LINPRIM_OCTAHEDRON) ? 0 : __float_as_int(pw[R_FACEMAP - R_PLANES]);
-            }
+            const float2 w = words[bcur * 16];
             const uint32_t e = e0 + (uint32_t)bcur;
             float acc[kGradWords];
-            const bool contributed = bwd_step<KIND, EXACT>(R, act && (int)e < last, pxf, pyf, rn, G0, G1, G2, T, GB, acc);
+            const bool contributed = bwd_step_exact<KIND>(w, act && (int)e < last, pxf, pyf, rn, G0, G1, G2, T, GB, acc);
             if (__ballot(contributed) != 0) {
                 float t0, t1;
                 int w0, w1;
@@ -1268,10 +1311,10 @@ static void bwd_dispatch(const ViewLayout& Lv, hipStream_t s, const ViewInfo* vi
                          const Status* st, uint64_t cap, const float bg[3], const float* T, const int32_t* last,
                          const float* grad, float* grads, const uint32_t* order) {
     if (EXACT)
-        hipLaunchKernelGGL((k_render_bwd_rows<TILE, KIND, true>), wave_grid<TILE>(Lv), dim3(64), 0, s, views, nv, n,
+        hipLaunchKernelGGL((k_render_bwd_rows<TILE, KIND>), wave_grid<TILE>(Lv), dim3(64), 0, s, views, nv, n,
                            payload, vals, ranges, offsets, st, cap, bg[0], bg[1], bg[2], T, last, grad, grads, order);
     else
-        hipLaunchKernelGGL((k_render_bwd<TILE, KIND, false>), wave_grid<TILE>(Lv), dim3(64), 0, s, views, nv, n,
+        hipLaunchKernelGGL((k_render_bwd<TILE, KIND>), wave_grid<TILE>(Lv), dim3(64), 0, s, views, nv, n,
                            payload, vals, ranges, offsets, st, cap, bg[0], bg[1], bg[2], T, last, grad, grads, order);
 }
 
