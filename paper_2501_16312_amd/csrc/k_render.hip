@@ -252,18 +252,7 @@ __device__ inline void exact_plane(float u, float c, int k, ExactPlanes& X) {
     X.L = fmaxf(X.L, X.lo[k]);
 }
 
-template <int KIND>
-__device__ inline void exact_planes(const Rec& R, float ki, float kj, ExactPlanes& X) {
-#pragma clang fp contract(off)
-    X.U = INFINITY;
-    X.L = -INFINITY;
-#pragma unroll
-    for (int k = 0; k < 4; ++k)
-        exact_plane<KIND>(__builtin_fmaf(R.p[4 * k + 0], ki, __builtin_fmaf(R.p[4 * k + 1], kj, R.p[4 * k + 2])),
-                          R.p[4 * k + 3], k, X);
-}
-
-// The same from a record spread over the row (see chord_row).
+// All four, from a record spread over the row (see chord_row).
 template <int KIND>
 __device__ inline void exact_planes_row(float2 r, float ki, float kj, ExactPlanes& X) {
     float u0 = row_word<10>(r), u1 = row_word<14>(r), u2 = row_word<18>(r), u3 = row_word<22>(r);
