@@ -155,9 +155,12 @@ int read_back(const void* src, uint64_t* dst, int words, hipStream_t s) {
         return LINPRIM_ERR_HIP;
     }
     if (ReadSlot* slot = take_slot()) {
-        const uint64_t seq = g_read_seq.fetch_add(1);
-        hipLaunchKernelGGL(k_read_back, dim3(1), dim3(64), 0, s, static_cast<const uint64_t*>(src), words, slot, seq);
-        if (hipGetLastError() == hipSuccess) {
+        uint64_t seq = g_read_seq.fetch_add(1);
+        const uint64_t* from = static_cast<const uint64_t*>(src);
+        void* args[] = {&from, &words, &slot, &seq};
+        // the launch's own status: the thread's last error may be another
+        // call's, and a slot given back for it would still be written to
+        if (hipLaunchKernel(reinterpret_cast<const void*>(k_read_back), dim3(1), dim3(64), args, 0, s) == hipSuccess) {
             const auto t0 = std::chrono::steady_clock::now();
             bool here = false;
             while (!(here = __atomic_load_n(&slot->seq, __ATOMIC_ACQUIRE) == seq)) {
@@ -172,6 +175,7 @@ int read_back(const void* src, uint64_t* dst, int words, hipStream_t s) {
             give_slot(slot);
             if (here) return LINPRIM_OK;
         } else {
+            (void)hipGetLastError();
             give_slot(slot);
         }
     }
