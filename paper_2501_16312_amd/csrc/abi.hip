@@ -147,14 +147,21 @@ void give_slot(ReadSlot* slot) {
 }
 
 // words (at most kReadWords) 8-byte words at src, as of the end of the work
-// enqueued on the stream.  Not under capture.
+// enqueued on the stream.  Refused where waiting for the stream is refused:
+// under its own capture (which stays valid), and while a capture is under way
+// that forbids such calls.  A wait that polls would pass by that rule, and meet
+// it only where it took longer than kPollMicros; hipFree(nullptr) applies it
+// (0.08 us; hipStreamQuery, 15 us behind launches).  The null stream may be
+// waited for during any capture of another stream; a kernel launch on it may
+// not, where that stream is a blocking one.
 int read_back(const void* src, uint64_t* dst, int words, hipStream_t s) {
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(s, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) {
-        (void)hipGetLastError();
-        return LINPRIM_ERR_HIP;
-    }
-    if (ReadSlot* slot = take_slot()) {
+    const hipError_t known = hipStreamIsCapturing(s, &cap);
+    const bool may_launch = known == hipSuccess;
+    const bool may_wait = cap == hipStreamCaptureStatusNone && (s ? may_launch && hipFree(nullptr) == hipSuccess : true);
+    if (!may_launch || (!may_wait && cap == hipStreamCaptureStatusNone)) (void)hipGetLastError();   // theirs
+    if (!may_wait) return LINPRIM_ERR_HIP;
+    if (ReadSlot* slot = may_launch ? take_slot() : nullptr) {
         uint64_t seq = g_read_seq.fetch_add(1);
         const uint64_t* from = static_cast<const uint64_t*>(src);
         void* args[] = {&from, &words, &slot, &seq};
@@ -167,8 +174,15 @@ int read_back(const void* src, uint64_t* dst, int words, hipStream_t s) {
                 if (std::chrono::steady_clock::now() - t0 > std::chrono::microseconds(kPollMicros)) break;
                 __builtin_ia32_pause();
             }
-            // a slot that a failed stream may still write to is not used again
-            if (!here && hipStreamSynchronize(s) != hipSuccess) return LINPRIM_ERR_HIP;
+            if (!here) {
+                // relaxed: a capture that began meanwhile is not disturbed
+                hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+                const bool swapped = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
+                const hipError_t e = hipStreamSynchronize(s);
+                if (swapped) (void)hipThreadExchangeStreamCaptureMode(&mode);
+                // a slot that a failed stream may still write to is not used again
+                if (e != hipSuccess) return LINPRIM_ERR_HIP;
+            }
             here = here || __atomic_load_n(&slot->seq, __ATOMIC_ACQUIRE) == seq;
             if (here)
                 for (int k = 0; k < words; ++k) dst[k] = __atomic_load_n(&slot->word[k], __ATOMIC_RELAXED);

@@ -1,6 +1,7 @@
 """Counts read back while something else on the thread or the device is in an
 unusual state."""
 import ctypes
+import threading
 
 import pytest
 import torch
@@ -50,3 +51,43 @@ def test_error_pending_from_another_call():
     finally:
         hip.hipGetLastError()
     assert _pair_count(r) == (L.OK, want)
+
+
+MODES = {"global": 0, "thread_local": 1, "relaxed": 2}
+
+
+@pytest.mark.parametrize("mode", list(MODES))
+@pytest.mark.parametrize("captured", ["blocking", "nonblocking"])
+@pytest.mark.parametrize("on", ["null", "other"])
+@pytest.mark.parametrize("thread", ["same", "another"])
+def test_while_another_stream_is_captured(mode, captured, on, thread):
+    """As a copy and a stream synchronisation: the null stream may be waited
+    for; another stream not, where the capture's mode forbids unsafe calls on
+    this thread, and then the capture ends in an error too."""
+    print(f"read back on the {on} stream, {thread} thread, capture of a {captured} stream, {mode}", flush=True)
+    hip = _hip()
+    r, want = _binned()
+    s, o, g = ctypes.c_void_p(), ctypes.c_void_p(), ctypes.c_void_p()
+    assert hip.hipStreamCreateWithFlags(ctypes.byref(s), 1 if captured == "nonblocking" else 0) == 0
+    assert hip.hipStreamCreateWithFlags(ctypes.byref(o), 1) == 0
+    got = []
+    call = lambda: got.append(_pair_count(r, None if on == "null" else o))
+    assert hip.hipStreamBeginCapture(s, MODES[mode]) == 0
+    if thread == "same":
+        call()
+    else:
+        t = threading.Thread(target=call)
+        t.start()
+        t.join()
+    ended = hip.hipStreamEndCapture(s, ctypes.byref(g))
+    hip.hipGetLastError()
+    if g.value:
+        hip.hipGraphDestroy(g)
+    hip.hipStreamDestroy(s)
+    refused = on == "other" and (mode == "global" or (mode == "thread_local" and thread == "same"))
+    if refused:
+        assert got[0][0] == L.ERR_HIP and ended != 0
+    else:
+        assert got[0] == (L.OK, want) and ended == 0
+    assert _pair_count(r, o) == (L.OK, want)
+    hip.hipStreamDestroy(o)
