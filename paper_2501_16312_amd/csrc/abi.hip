@@ -146,6 +146,17 @@ void give_slot(ReadSlot* slot) {
     g_read_used &= ~(uint64_t(1) << (slot - g_read_page));
 }
 
+// Whether a kernel on the stream may read src as 8-byte words: device memory of
+// the stream's own device.  (Another device's, or host memory, which a copy
+// takes as well, would fault there.  0.15 us.)
+bool readable_by(hipStream_t s, const void* src) {
+    hipPointerAttribute_t at;
+    hipDevice_t dev = -1;
+    const bool known = hipStreamGetDevice(s, &dev) == hipSuccess && hipPointerGetAttributes(&at, src) == hipSuccess;
+    if (!known) (void)hipGetLastError();
+    return known && at.type == hipMemoryTypeDevice && at.device == dev && ((uintptr_t)src & 7) == 0;
+}
+
 // words (at most kReadWords) 8-byte words at src, as of the end of the work
 // enqueued on the stream.  Refused where waiting for the stream is refused:
 // under its own capture (which stays valid), and while a capture is under way
@@ -161,7 +172,7 @@ int read_back(const void* src, uint64_t* dst, int words, hipStream_t s) {
     const bool may_wait = cap == hipStreamCaptureStatusNone && (s ? may_launch && hipFree(nullptr) == hipSuccess : true);
     if (!may_launch || (!may_wait && cap == hipStreamCaptureStatusNone)) (void)hipGetLastError();   // theirs
     if (!may_wait) return LINPRIM_ERR_HIP;
-    if (ReadSlot* slot = may_launch ? take_slot() : nullptr) {
+    if (ReadSlot* slot = may_launch && readable_by(s, src) ? take_slot() : nullptr) {
         uint64_t seq = g_read_seq.fetch_add(1);
         const uint64_t* from = static_cast<const uint64_t*>(src);
         void* args[] = {&from, &words, &slot, &seq};

@@ -15,7 +15,7 @@ pytestmark = pytest.mark.gpu
 
 def _hip():
     """The HIP runtime this process runs on."""
-    torch.zeros(1, device="cuda")
+    torch.cuda.init()
     with open("/proc/self/maps") as f:
         path = next(line.split()[-1] for line in f if "libamdhip64" in line)
     return ctypes.CDLL(path)
@@ -91,3 +91,22 @@ def test_while_another_stream_is_captured(mode, captured, on, thread):
         assert got[0] == (L.OK, want) and ended == 0
     assert _pair_count(r, o) == (L.OK, want)
     hip.hipStreamDestroy(o)
+
+
+@pytest.mark.parametrize("device,pinned,shift", [("cpu", False, 0), ("cpu", False, 4), ("cpu", True, 0),
+                                                 ("cpu", True, 4), ("cuda", False, 4)])
+def test_status_words_a_kernel_may_not_read(device, pinned, shift):
+    """A status block in host memory, or off the 8-byte alignment, is answered
+    as the copy answers it: taken, but for host memory that is not pinned."""
+    print(f"read back from {device}, pinned {pinned}, {shift} bytes off", flush=True)
+    r, want = _binned()
+    n, over = ctypes.c_int64(-1), ctypes.c_int32(-1)
+    buf = torch.zeros(256 + shift, dtype=torch.uint8, device=device, pin_memory=pinned)
+    buf[shift:shift + 64].copy_(r.view_ws[:64])
+    torch.cuda.synchronize()
+    rc = L.load().linprim_read_status(ctypes.c_void_p(buf.data_ptr() + shift), ctypes.byref(n), ctypes.byref(over),
+                                      None)
+    _hip().hipGetLastError()           # of a refused copy
+    taken = device == "cuda" or pinned
+    assert (rc, n.value, over.value) == ((L.OK, want, 0) if taken else (L.ERR_HIP, -1, -1))
+    assert _pair_count(r) == (L.OK, want)
