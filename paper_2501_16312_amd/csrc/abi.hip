@@ -146,6 +146,14 @@ void give_slot(ReadSlot* slot) {
     g_read_used &= ~(uint64_t(1) << (slot - g_read_page));
 }
 
+// The words by a copy and a stream synchronisation.  Allocates nothing.
+int copy_back(const void* src, uint64_t* dst, int words, hipStream_t s) {
+    if (hipMemcpyAsync(dst, src, sizeof(uint64_t) * (size_t)words, hipMemcpyDeviceToHost, s) != hipSuccess ||
+        hipStreamSynchronize(s) != hipSuccess)
+        return LINPRIM_ERR_HIP;
+    return LINPRIM_OK;
+}
+
 // Whether a kernel on the stream may read src as 8-byte words: device memory of
 // the stream's own device.  (Another device's, or host memory, which a copy
 // takes as well, would fault there.  0.15 us.)
@@ -204,10 +212,7 @@ int read_back(const void* src, uint64_t* dst, int words, hipStream_t s) {
             give_slot(slot);
         }
     }
-    if (hipMemcpyAsync(dst, src, sizeof(uint64_t) * (size_t)words, hipMemcpyDeviceToHost, s) != hipSuccess ||
-        hipStreamSynchronize(s) != hipSuccess)
-        return LINPRIM_ERR_HIP;
-    return LINPRIM_OK;
+    return copy_back(src, dst, words, s);
 }
 
 bool valid_tile(int t) { return t == 8 || t == 16 || t == 32; }
@@ -564,8 +569,9 @@ int linprim_densify_noalloc(int32_t type, int32_t sh_degree, int64_t n, const li
                             densify_params(params), params->extent, bs, s) != hipSuccess)
         return LINPRIM_ERR_HIP;
     const int64_t nb = (n + kDensifyItems - 1) / kDensifyItems;
+    // no read_back, whose first call of a process allocates the pinned page
     uint64_t total = 0;
-    if (int rc = read_back(bs + nb, &total, 1, s)) return rc;
+    if (int rc = copy_back(bs + nb, &total, 1, s)) return rc;
     *n_out = (int64_t)total;
     if (*n_out > dst_rows) return LINPRIM_ERR_WORKSPACE;
     return hip_status(launch_densify_apply(type, sh_degree, n, state_set(src), normals, grad_accum, count,
