@@ -120,23 +120,24 @@ __device__ inline void emit_wave(const Pair& pair, int64_t t, int64_t n_vis, con
     }
 }
 
-// Every pair of every visible slot, by the whole grid.
-template <class Pair>
+// Every pair of every visible slot, by the whole grid: per_wave slots at a time
+// to a wave; huge runs in 64-pair chunks dealt round-robin over all waves, or
+// (BINS) whole runs dealt over the blocks.
+template <bool BINS, class Pair>
 __device__ inline void emit_all(const Pair& pair, const uint32_t* __restrict__ depth_keys,
                                 const uint32_t* __restrict__ tiles, const uint32_t* __restrict__ offsets,
                                 const uint2* __restrict__ trect, const ViewInfo* __restrict__ views,
                                 const uint32_t* __restrict__ vis, int64_t n, const Status* __restrict__ status,
-                                const uint32_t* __restrict__ huge) {
+                                const uint32_t* __restrict__ huge, int per_wave) {
     const int lane = threadIdx.x & 63;
     const int64_t n_vis = status->n_vis;
-    // a grid of a few waves per CU strides over the list, 64 slots at a time
+    // a grid of a few waves per CU strides over the list
     const int64_t n_waves = (int64_t)gridDim.x * (blockDim.x >> 6);
     const int64_t wave_id = (int64_t)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
-    for (int64_t w0 = wave_id * 64; w0 < n_vis; w0 += n_waves * 64)
-        emit_wave(pair, w0 + lane, n_vis, depth_keys, tiles, offsets, trect, views, vis, n);
-    // huge runs: 64-pair chunks dealt round-robin over all waves
+    for (int64_t w0 = wave_id * per_wave; w0 < n_vis; w0 += n_waves * per_wave)
+        emit_wave(pair, lane < per_wave ? w0 + lane : n_vis, n_vis, depth_keys, tiles, offsets, trect, views, vis, n);
     const uint32_t n_huge = status->n_huge;
-    for (uint32_t i = 0; i < n_huge; ++i) {
+    for (uint32_t i = BINS ? blockIdx.x : 0u; i < n_huge; i += BINS ? gridDim.x : 1u) {
         const int64_t vs = huge[i];
         const int v = (int)(vs / n);
         const uint32_t prim = (uint32_t)(vs - (int64_t)v * n);
@@ -146,7 +147,9 @@ __device__ inline void emit_all(const Pair& pair, const uint32_t* __restrict__ d
         const uint32_t bn = tr.y & 0xffffu;
         const ViewInfo& V = views[v];
         const uint64_t bg = (uint64_t)(V.tile_base + (int64_t)ty0 * V.tiles_x + tx0);
-        for (int64_t q0 = wave_id * 64; q0 < (int64_t)c; q0 += n_waves * 64) {
+        const int64_t first = BINS ? (int64_t)(threadIdx.x & ~63u) : wave_id * 64;
+        const int64_t stride = BINS ? (int64_t)blockDim.x : n_waves * 64;
+        for (int64_t q0 = first; q0 < (int64_t)c; q0 += stride) {
             const uint32_t q = (uint32_t)q0 + (uint32_t)lane;
             if (q < c) {
                 const uint32_t row = q / bn, col = q - row * bn;
@@ -173,7 +176,7 @@ __global__ __launch_bounds__(256) void k_emit_pairs(const uint32_t* __restrict__
         if (blockIdx.x == 0 && threadIdx.x == 0) status->overflow = 1;
         return;
     }
-    emit_all(WritePair{keys, vals}, depth_keys, tiles, offsets, trect, views, vis, n, status, huge);
+    emit_all<false>(WritePair{keys, vals}, depth_keys, tiles, offsets, trect, views, vis, n, status, huge, 64);
 }
 
 // ---------------------------------------------------------------------------
@@ -190,6 +193,22 @@ __global__ __launch_bounds__(256) void k_emit_pairs(const uint32_t* __restrict__
 // ---------------------------------------------------------------------------
 constexpr int kBinThreads = 512;
 constexpr int64_t kBinBlocks = 128;
+// A wave takes the slots of about this many pairs, at most 64: with few slots of
+// many tiles each, 64 to a wave left the chip to a few waves that wrote one run
+// after the other, three times, and every wave walked every huge run (700
+// octahedra, 113k pairs: bin_sort 149 us, by the radix passes 68, now 31; 40
+// octahedra, 21k pairs: 108, 68, 31; at 64, 256 and 512 pairs to a wave 700 at
+// 16-pixel tiles take 23, 28 and 36 us, at 128 24; 3000 in 16 views 31, 28 and
+// 28, at 128 28).
+constexpr int64_t kBinWavePairs = 128;
+__device__ inline int bin_slots(const Status* __restrict__ status) {
+    const uint64_t per = kBinWavePairs * (uint64_t)status->n_vis / max(status->n_pairs, (unsigned long long)1);
+    return (int)min(max(per, (uint64_t)1), (uint64_t)64);
+}
+// Whether a block of the binning kernels has a slot to take.
+__device__ inline bool bin_idle(const Status* __restrict__ status, int per_wave) {
+    return (int64_t)blockIdx.x * (kBinThreads / 64) * per_wave >= (int64_t)status->n_vis && blockIdx.x >= status->n_huge;
+}
 
 __global__ __launch_bounds__(kBinThreads) void k_count_tiles(const uint32_t* __restrict__ depth_keys,
                                                              const uint32_t* __restrict__ tiles,
@@ -206,10 +225,11 @@ __global__ __launch_bounds__(kBinThreads) void k_count_tiles(const uint32_t* __r
         if (blockIdx.x == 0 && threadIdx.x == 0) status->overflow = 1;
         return;
     }
-    if ((int64_t)blockIdx.x * kBinThreads >= (int64_t)status->n_vis && status->n_huge == 0) return;
+    const int per_wave = bin_slots(status);
+    if (bin_idle(status, per_wave)) return;
     for (int g = threadIdx.x; g < n_tiles; g += kBinThreads) bins[g] = 0u;
     __syncthreads();
-    emit_all(CountPair{bins}, depth_keys, tiles, offsets, trect, views, vis, n, status, huge);
+    emit_all<true>(CountPair{bins}, depth_keys, tiles, offsets, trect, views, vis, n, status, huge, per_wave);
     __syncthreads();
     for (int g = threadIdx.x; g < n_tiles; g += kBinThreads)
         if (bins[g]) atomicAdd(counts + g, bins[g]);
@@ -227,16 +247,17 @@ __global__ __launch_bounds__(kBinThreads) void k_place_pairs(const uint32_t* __r
                                                              uint64_t* __restrict__ keys, uint32_t* __restrict__ vals) {
     extern __shared__ uint32_t bins[];
     if (status->n_pairs > capacity) return;
-    if ((int64_t)blockIdx.x * kBinThreads >= (int64_t)status->n_vis && status->n_huge == 0) return;
+    const int per_wave = bin_slots(status);
+    if (bin_idle(status, per_wave)) return;
     for (int g = threadIdx.x; g < n_tiles; g += kBinThreads) bins[g] = 0u;
     __syncthreads();
-    emit_all(CountPair{bins}, depth_keys, tiles, offsets, trect, views, vis, n, status, huge);
+    emit_all<true>(CountPair{bins}, depth_keys, tiles, offsets, trect, views, vis, n, status, huge, per_wave);
     __syncthreads();
     // the block's run of every tile it touches
     for (int g = threadIdx.x; g < n_tiles; g += kBinThreads)
         if (bins[g]) bins[g] = atomicAdd(cursor + g, bins[g]);
     __syncthreads();
-    emit_all(PlacePair{bins, keys, vals}, depth_keys, tiles, offsets, trect, views, vis, n, status, huge);
+    emit_all<true>(PlacePair{bins, keys, vals}, depth_keys, tiles, offsets, trect, views, vis, n, status, huge, per_wave);
 }
 
 // ---------------------------------------------------------------------------
@@ -1035,8 +1056,11 @@ hipError_t launch_bin_sort(const ViewLayout& L, char* vws, const PairLayout& P, 
             kin = kb; kout = ka;
             vin = vb; vout = va;
         }
-        const int64_t bb = (vn + kBinThreads - 1) / kBinThreads;
-        const dim3 bin_grid((unsigned)(bb < kBinBlocks ? bb : kBinBlocks));
+        // blocks for 64 slots to a wave, and for waves of few slots
+        const int64_t by_slots = (vn + kBinThreads - 1) / kBinThreads;
+        const int64_t by_pairs = (P.capacity + kBinWavePairs * (kBinThreads / 64) - 1) / (kBinWavePairs * (kBinThreads / 64));
+        const int64_t bb = by_slots > by_pairs ? by_slots : by_pairs;
+        const dim3 bin_grid((unsigned)(bb < 1 ? 1 : bb < kBinBlocks ? bb : kBinBlocks));
         const unsigned lds = (unsigned)nt * 4;
         hipLaunchKernelGGL(k_count_tiles, bin_grid, dim3(kBinThreads), lds, stream, depth_keys, tiles, offsets, trect,
                            views, vis, L.n, status, cap, huge, (int)nt, counts);
