@@ -403,7 +403,7 @@ __device__ inline double centre_depth(const ViewInfo& V, const float* __restrict
     return exact ? t2 : sqrt(t0 * t0 + t1 * t1 + t2 * t2);
 }
 
-// Whether no pixel centre of a quad can have a chord through the primitive,
+// Whether no pixel centre of a quad can have a chord through the octahedron,
 // for the quads at x = qx and qx + 4 and y = qy (bits 0 and 1).  A chord needs
 // every upper plane above every lower one at the pixel; the difference of two
 // planes is linear, so over the part of the quad inside the pixel rectangle it
@@ -414,7 +414,6 @@ __device__ inline double centre_depth(const ViewInfo& V, const float* __restrict
 // |A| Kx + |B| Ky + |D| of a plane; 64 eps M is taken.  A NaN or an infinite M
 // keeps the entry.
 // Planes are read one pair at a time, in order, to take few registers.
-template <int KIND>
 __device__ inline uint32_t quads_missed(const float* rec, float gx, float gy, float qy) {
     const float bx = rec[4], by = rec[5], bw = rec[6], bh = rec[7];
     const float* w = rec + 8;
@@ -430,39 +429,20 @@ __device__ inline uint32_t quads_missed(const float* rec, float gx, float gy, fl
         hx[q] = 0.5f * (x1 - x0);
         least[q] = INFINITY;
     }
-    if (KIND == LINPRIM_OCTAHEDRON) {
 #pragma unroll
-        for (int a = 0; a < 4; ++a) {
-            const float p0 = w[4 * a], p1 = w[4 * a + 1], p2 = w[4 * a + 2], p3 = w[4 * a + 3];
-            m = fmaxf(m, __builtin_fmaf(fabsf(p0), kx, __builtin_fmaf(fabsf(p1), ky, fmaxf(fabsf(p2), fabsf(p3)))));
+    for (int a = 0; a < 4; ++a) {
+        const float p0 = w[4 * a], p1 = w[4 * a + 1], p2 = w[4 * a + 2], p3 = w[4 * a + 3];
+        m = fmaxf(m, __builtin_fmaf(fabsf(p0), kx, __builtin_fmaf(fabsf(p1), ky, fmaxf(fabsf(p2), fabsf(p3)))));
 #pragma unroll
-            for (int b = a + 1; b < 4; ++b) {
-                const float da = p0 - w[4 * b], db = p1 - w[4 * b + 1], up = p2 - w[4 * b + 3], dn = w[4 * b + 2] - p3;
-                const float my = db * cy, ey = fabsf(db) * hy;
+        for (int b = a + 1; b < 4; ++b) {
+            const float da = p0 - w[4 * b], db = p1 - w[4 * b + 1], up = p2 - w[4 * b + 3], dn = w[4 * b + 2] - p3;
+            const float my = db * cy, ey = fabsf(db) * hy;
 #pragma unroll
-                for (int q = 0; q < 2; ++q) {
-                    const float mid = __builtin_fmaf(da, cx[q], my), ext = __builtin_fmaf(fabsf(da), hx[q], ey);
-                    least[q] = fminf(least[q], fminf((ext + mid) + up, (ext - mid) + dn));
-                }
-                asm volatile("" : "+v"(least[0]), "+v"(least[1]), "+v"(m) : : "memory");
+            for (int q = 0; q < 2; ++q) {
+                const float mid = __builtin_fmaf(da, cx[q], my), ext = __builtin_fmaf(fabsf(da), hx[q], ey);
+                least[q] = fminf(least[q], fminf((ext + mid) + up, (ext - mid) + dn));
             }
-        }
-    } else {
-#pragma unroll
-        for (int a = 0; a < 3; ++a) {
-            const float p0 = w[3 * a], p1 = w[3 * a + 1], p2 = w[3 * a + 2];
-            m = fmaxf(m, __builtin_fmaf(fabsf(p0), kx, __builtin_fmaf(fabsf(p1), ky, fabsf(p2))));
-#pragma unroll
-            for (int b = 0; b < 3; ++b) {
-                const float q0 = w[9 + 3 * b], q1 = w[10 + 3 * b], q2 = w[11 + 3 * b];
-                if (a == 0) m = fmaxf(m, __builtin_fmaf(fabsf(q0), kx, __builtin_fmaf(fabsf(q1), ky, fabsf(q2))));
-                const float da = p0 - q0, db = p1 - q1;
-                const float my = __builtin_fmaf(fabsf(db), hy, __builtin_fmaf(db, cy, p2 - q2));
-#pragma unroll
-                for (int q = 0; q < 2; ++q)
-                    least[q] = fminf(least[q], __builtin_fmaf(fabsf(da), hx[q], __builtin_fmaf(da, cx[q], my)));
-                asm volatile("" : "+v"(least[0]), "+v"(least[1]), "+v"(m) : : "memory");
-            }
+            asm volatile("" : "+v"(least[0]), "+v"(least[1]), "+v"(m) : : "memory");
         }
     }
     const float margin = -0x1p-18f * m;
@@ -477,7 +457,10 @@ __device__ inline uint32_t quads_missed(const float* rec, float gx, float gy, fl
 // kernel 120 -> 88 us; from 16 or 25 on 88 and 94, and 41 -> 43 us from 16 on
 // for a training view whose entries meet 1.8 quads).  8-pixel tiles, whose
 // lists hold smaller rectangles, go without it: the registers it takes cost
-// them more (1M octahedra at 1080p 71 -> 74 us, 16 views of 500k 370 -> 382).
+// them more (1M octahedra at 1080p 71 -> 74 us, 16 views of 500k 370 -> 382), and
+// so do tetrahedra, which fill more of their rectangles: 20k at 1080p, 0.05-0.3
+// wide, 16-pixel tiles 76 us without it, 103 with it; 200k 74 and 103; 500k of a
+// room 74 and 90.
 constexpr int kOutlineSteps = 20;
 
 template <int TILE, int KIND, bool COUNT, bool EXACT, bool DEPTH>
@@ -513,7 +496,7 @@ __global__ __launch_bounds__(64, 6) void k_render_fwd(const ViewInfo* __restrict
     float half_entry = 0.0f;       // its entry depth relative to its centre
     const float* base = payload + (size_t)P.v * (size_t)n * kRecordWords;
     // counted renders count every pixel of a rectangle
-    constexpr bool kOutline = NQ > 1 && !EXACT && !COUNT;
+    constexpr bool kOutline = NQ > 1 && KIND == LINPRIM_OCTAHEDRON && !EXACT && !COUNT;
     uint32_t seen = 0;             // the batch's last blended entry, from 1
     auto blend = [&](float2 words, uint32_t e) {
         // Branch-free: lanes that do not see the primitive blend with
@@ -635,7 +618,7 @@ __global__ __launch_bounds__(64, 6) void k_render_fwd(const ViewInfo* __restrict
                                   max(__builtin_popcount(m2), __builtin_popcount(m3)));
             if (steps >= kOutlineSteps) {
                 // lanes l and l + 32 test the upper and the lower quads of entry l
-                const uint32_t missed = quads_missed<KIND>(reinterpret_cast<const float*>(srec[sl]), gx, gy,
+                const uint32_t missed = quads_missed(reinterpret_cast<const float*>(srec[sl]), gx, gy,
                                                            lane < 32 ? gy : gy + 4.0f);
                 const uint64_t xl = __builtin_amdgcn_ballot_w64(missed & 1u), xr = __builtin_amdgcn_ballot_w64(missed & 2u);
                 m0 &= ~(uint32_t)xl;
