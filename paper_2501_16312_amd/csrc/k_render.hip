@@ -392,8 +392,12 @@ constexpr float kDepthT = 0.5f;
 // same entry (and LDS records for lists of more than 128): 93 us for 1M
 // octahedra at 1080p, 568 for 16 views of 500k, 992 for 8 views of 3M; now 69,
 // 358 and 570.  Large primitives, whose rectangles meet every quad, gain
-// nothing from the split, and lose nothing: 124 -> 121 us for a depth map of
-// 500k with 2.9 quads an entry at 16-pixel tiles (88 with the outlines' test).
+// nothing from the split: 124 -> 121 us for a depth map of 500k with 2.9 quads an
+// entry at 16-pixel tiles (88 with the outlines' test), and where a crowd of
+// opaque ones fills every quad the step's own cost shows: a step is 44 VALU
+// instructions (46 with a select for the empty mask and entries counted from 1)
+// against 39 of the wave-uniform walk (20k octahedra 0.05-0.3 wide at 1080p,
+// 8-pixel tiles: 57 us, now 59; 20k tetrahedra 76 and 79).
 // Wider tiles first filter the list for the group, so that batches are full.
 __device__ inline double centre_depth(const ViewInfo& V, const float* __restrict__ means, uint32_t prim, bool exact) {
     const double x = means[3 * (size_t)prim], y = means[3 * (size_t)prim + 1], z = means[3 * (size_t)prim + 2];
@@ -473,7 +477,8 @@ __global__ __launch_bounds__(64, 6) void k_render_fwd(const ViewInfo* __restrict
                                                    unsigned long long* __restrict__ counters,
                                                    const float* __restrict__ means,
                                                    float* __restrict__ out_depth, const uint32_t* __restrict__ order) {
-    __shared__ float4 srec[33][8];
+    __shared__ float4 store[33][8];
+    float4 (*srec)[8] = store + 1;
     __shared__ uint2 queue[(TILE == 8) ? 1 : 96];   // (primitive, list position) of entries that meet the group
     if (status->n_pairs > capacity) return;
     constexpr int QX = TILE / 8, NQ = QX * QX;
@@ -497,7 +502,7 @@ __global__ __launch_bounds__(64, 6) void k_render_fwd(const ViewInfo* __restrict
     const float* base = payload + (size_t)P.v * (size_t)n * kRecordWords;
     // counted renders count every pixel of a rectangle
     constexpr bool kOutline = NQ > 1 && KIND == LINPRIM_OCTAHEDRON && !EXACT && !COUNT;
-    uint32_t seen = 0;             // the batch's last blended entry, from 1
+    uint32_t seen = ~0u;           // the batch's last blended entry
     auto blend = [&](float2 words, uint32_t e) {
         // Branch-free: lanes that do not see the primitive blend with
         // 1 - o = 1 exactly, which leaves C and T unchanged.
@@ -533,10 +538,10 @@ __global__ __launch_bounds__(64, 6) void k_render_fwd(const ViewInfo* __restrict
             half_entry = cross ? entry : half_entry;
         }
         T = T * onemo;
-        seen = hitp ? e + 1 : seen;
+        seen = hitp ? e : seen;
         // T only falls where the primitive was hit
         const uint64_t stop = __builtin_amdgcn_ballot_w64(T <= kTStop) & m_hit;
-        if (COUNT) term = __builtin_amdgcn_inverse_ballot_w64(stop) ? e + 1 : term;
+        if (COUNT) term = __builtin_amdgcn_inverse_ballot_w64(stop) ? e : term;
         live &= ~stop;
     };
     constexpr int NQD = rec_quads<KIND, EXACT>(), NH = (NQD + 1) / 2;
@@ -548,8 +553,8 @@ __global__ __launch_bounds__(64, 6) void k_render_fwd(const ViewInfo* __restrict
 #pragma unroll
         for (int k = 0; k < NH; ++k) st[k] = rp[1 + min((int)q0 + k, NQD - 1)];
     };
-    // entry 32: a record no pixel lies in, for a row without one
-    if (lane < 8) srec[32][lane] = (lane == 1) ? make_float4(0.f, 0.f, -1.f, -1.f) : make_float4(0.f, 0.f, 0.f, 0.f);
+    // entry -1: a record no pixel lies in, for a row without one
+    if (lane < 8) srec[-1][lane] = (lane == 1) ? make_float4(0.f, 0.f, -1.f, -1.f) : make_float4(0.f, 0.f, 0.f, 0.f);
     const float2* words = reinterpret_cast<const float2*>(srec[0]) + li;
     // The next up to 32 entries that meet the group: their number, their list
     // positions (lane l: entry l & 31), their records on the way.  A group-sized
@@ -633,19 +638,20 @@ __global__ __launch_bounds__(64, 6) void k_render_fwd(const ViewInfo* __restrict
         n_here = take(pos1);
         // inside the batch entries count from 0
         const uint32_t half0 = half, term0 = term;
-        seen = 0;
+        seen = ~0u;
         half = 0xffffffffu;
-        term = 0;
+        term = ~0u;
         auto next = [&](uint32_t& e, float2& w) {
-            e = mask ? (uint32_t)__builtin_ctz(mask) : 32u;
+            // the lowest set bit, ~0 for none (the compiler adds a select for that)
+            asm("v_ffbl_b32 %0, %1" : "=v"(e) : "v"(mask));
             mask &= mask - 1u;
-            w = words[e * 16u];
+            w = words[(int)e * 16];
         };
         uint32_t eA, eB;
         float2 wA, wB;
         next(eA, wA);
         next(eB, wB);
-        while (live && __builtin_amdgcn_ballot_w64(eA < 32u)) {
+        while (live && __builtin_amdgcn_ballot_w64((int)eA >= 0)) {
             blend(wA, eA);
             next(eA, wA);
             blend(wB, eB);
@@ -655,15 +661,15 @@ __global__ __launch_bounds__(64, 6) void k_render_fwd(const ViewInfo* __restrict
         auto list_pos = [&](uint32_t e) {
             return (NQ == 1) ? (uint32_t)__builtin_amdgcn_readfirstlane((int)pos) + e : (uint32_t)__shfl((int)pos, (int)(e & 31u));
         };
-        const uint32_t p_last = list_pos(seen - 1);
-        last = seen ? (int)p_last + 1 : last;
+        const uint32_t p_last = list_pos(seen);
+        last = (seen != ~0u) ? (int)p_last + 1 : last;
         if (DEPTH) {
             const uint32_t p_half = list_pos(half);
             half = (half != 0xffffffffu) ? p_half : half0;
         }
         if (COUNT) {
-            const uint32_t p_term = list_pos(term - 1);
-            term = term ? p_term + 1 : term0;
+            const uint32_t p_term = list_pos(term);
+            term = (term != ~0u) ? p_term + 1 : term0;
         }
         pos = pos1;
     }
