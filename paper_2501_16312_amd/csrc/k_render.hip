@@ -276,6 +276,17 @@ __device__ inline void exact_planes_row(float2 r, float ki, float kj, ExactPlane
 }
 #undef LP_FMAC_ROW
 
+// All four, from a whole record.
+template <int KIND>
+__device__ inline void exact_planes(const Rec& R, float ki, float kj, ExactPlanes& X) {
+    X.U = INFINITY;
+    X.L = -INFINITY;
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+        exact_plane<KIND>(__builtin_fmaf(R.p[4 * k + 0], ki, __builtin_fmaf(R.p[4 * k + 1], kj, R.p[4 * k + 2])),
+                          R.p[4 * k + 3], k, X);
+}
+
 // |D| (min exits - max entries) with rn = |D| of the pixel ray; the z_c
 // factor of the chord is folded into the record's sigma.
 __device__ inline float exact_chord(const ExactPlanes& X, float rn) {
@@ -467,6 +478,17 @@ __device__ inline uint32_t quads_missed(const float* rec, float gx, float gy, fl
 // room 74 and 90.
 constexpr int kOutlineSteps = 20;
 
+// Exact rays: where the wave, walking a batch together, takes no more than
+// kWaveSteps for every kRowSteps steps that its busiest row would take alone, it
+// does so, with records in scalar registers: a step is 64 VALU instructions
+// then, 69 with rows (20k octahedra 0.05-0.3 wide at 1080p, 8-pixel tiles: 75 us
+// by rows alone, 65 so and when the wave always walked together; at 16-pixel
+// tiles 79, 70 and 66; 300k of a room 33.0, 31.8 and 43; if no step may be lost,
+// 68 for the crowd).  Ray space, 39 against 44, stays with the rows: crowds would
+// gain (1M of a room 76 -> 72 us), but 16 views of 500k take 352 -> 378 and
+// tetrahedra at 16-pixel tiles 382 -> 408.
+constexpr int kRowSteps = 8, kWaveSteps = 9;
+
 template <int TILE, int KIND, bool COUNT, bool EXACT, bool DEPTH>
 __global__ __launch_bounds__(64, 6) void k_render_fwd(const ViewInfo* __restrict__ views, int n_views, int64_t n,
                                                    const float* __restrict__ payload, const uint32_t* __restrict__ vals,
@@ -503,35 +525,23 @@ __global__ __launch_bounds__(64, 6) void k_render_fwd(const ViewInfo* __restrict
     // counted renders count every pixel of a rectangle
     constexpr bool kOutline = NQ > 1 && KIND == LINPRIM_OCTAHEDRON && !EXACT && !COUNT;
     uint32_t seen = ~0u;           // the batch's last blended entry
-    auto blend = [&](float2 words, uint32_t e) {
-        // Branch-free: lanes that do not see the primitive blend with
-        // 1 - o = 1 exactly, which leaves C and T unchanged.
-        const float ki = pxf - row_word<4>(words), kj = pyf - row_word<5>(words);
+    auto in_box = [&](float ki, float kj, float wi, float wj) {
         // lane masks of single compares combine in scalar registers
-        const uint64_t m_in = __builtin_amdgcn_ballot_w64(fabsf(ki) <= row_word<6>(words)) &
-                              __builtin_amdgcn_ballot_w64(fabsf(kj) <= row_word<7>(words)) & live;
-        const bool inside = __builtin_amdgcn_inverse_ballot_w64(m_in);
-        float dch, entry = 0.0f;
-        if (EXACT) {
-            ExactPlanes X;
-            exact_planes_row<KIND>(words, ki, kj, X);
-            dch = exact_chord(X, rn);
-            entry = X.L;
-        } else {
-            dch = chord_row<KIND>(words, ki, kj, entry);
-        }
+        return __builtin_amdgcn_ballot_w64(fabsf(ki) <= wi) & __builtin_amdgcn_ballot_w64(fabsf(kj) <= wj) & live;
+    };
+    // Branch-free: lanes that do not see the primitive blend with
+    // 1 - o = 1 exactly, which leaves C and T unchanged.
+    auto composite = [&](uint64_t m_in, float dch, float entry, float eh, uint32_t e, auto add_colour) {
         const uint64_t m_hit = m_in & __builtin_amdgcn_ballot_w64(dch > 0.0f);
         const bool hitp = __builtin_amdgcn_inverse_ballot_w64(m_hit);
         if (COUNT) {
-            ev += inside ? 1u : 0u;
+            ev += __builtin_amdgcn_inverse_ballot_w64(m_in) ? 1u : 0u;
             hit += hitp ? 1u : 0u;
         }
-        // broadcasts run with every lane: outside the selection
-        const float eh = chord_exp(row_word<0>(words), dch);
         const float ex = hitp ? eh : 1.0f;
         const float onemo = fmaxf(ex, kOneMinusOMax);
         const float w = T * (1.0f - onemo);
-        add_colour_row(words, w, C0, C1, C2);
+        add_colour(w);
         if (DEPTH) {
             const bool cross = T >= kDepthT && T * onemo < kDepthT;
             half = cross ? e : half;
@@ -543,6 +553,36 @@ __global__ __launch_bounds__(64, 6) void k_render_fwd(const ViewInfo* __restrict
         const uint64_t stop = __builtin_amdgcn_ballot_w64(T <= kTStop) & m_hit;
         if (COUNT) term = __builtin_amdgcn_inverse_ballot_w64(stop) ? e : term;
         live &= ~stop;
+    };
+    // an entry of each row's own, its record spread over the row
+    auto blend = [&](float2 words, uint32_t e) {
+        const float ki = pxf - row_word<4>(words), kj = pyf - row_word<5>(words);
+        const uint64_t m_in = in_box(ki, kj, row_word<6>(words), row_word<7>(words));
+        float dch, entry = 0.0f;
+        if (EXACT) {
+            ExactPlanes X;
+            exact_planes_row<KIND>(words, ki, kj, X);
+            dch = exact_chord(X, rn);
+            entry = X.L;
+        } else {
+            dch = chord_row<KIND>(words, ki, kj, entry);
+        }
+        // broadcasts run with every lane: outside the selection
+        composite(m_in, dch, entry, chord_exp(row_word<0>(words), dch), e,
+                  [&](float w) { add_colour_row(words, w, C0, C1, C2); });
+    };
+    // one entry for the whole wave, its record in scalar registers
+    auto blend_together = [&](const Rec& R, uint32_t e) {
+        const float ki = pxf - R.fi0, kj = pyf - R.fj0;
+        const uint64_t m_in = in_box(ki, kj, R.fwi, R.fwj);
+        ExactPlanes X;
+        exact_planes<KIND>(R, ki, kj, X);
+        const float dch = exact_chord(X, rn);
+        composite(m_in, dch, X.L, chord_exp(R.s2, dch), e, [&](float w) {
+            C0 = __builtin_fmaf(w, R.r, C0);
+            C1 = __builtin_fmaf(w, R.g, C1);
+            C2 = __builtin_fmaf(w, R.b, C2);
+        });
     };
     constexpr int NQD = rec_quads<KIND, EXACT>(), NH = (NQD + 1) / 2;
     const uint32_t sl = (uint32_t)lane & 31u, q0 = ((uint32_t)lane >> 5) * NH;
@@ -557,8 +597,9 @@ __global__ __launch_bounds__(64, 6) void k_render_fwd(const ViewInfo* __restrict
     if (lane < 8) srec[-1][lane] = (lane == 1) ? make_float4(0.f, 0.f, -1.f, -1.f) : make_float4(0.f, 0.f, 0.f, 0.f);
     const float2* words = reinterpret_cast<const float2*>(srec[0]) + li;
     // The next up to 32 entries that meet the group: their number, their list
-    // positions (lane l: entry l & 31), their records on the way.  A group-sized
-    // tile takes its list as it is; others filter it, 64 entries at a time.
+    // positions and primitives (lane l: entry l & 31), their records on the way.
+    // A group-sized tile takes its list as it is; others filter it, 64 entries at
+    // a time.
     constexpr uint32_t CH = (NQ == 1) ? 32 : 64;
     uint32_t ce = rg.x, qn = 0;
     auto chunk = [&](uint32_t e) {
@@ -568,11 +609,12 @@ __global__ __launch_bounds__(64, 6) void k_render_fwd(const ViewInfo* __restrict
     uint32_t idx0 = chunk(ce), idx1 = chunk(ce + CH);
     int4 rect = make_int4(0, 0, 0, 0);
     if (NQ > 1) rect = *reinterpret_cast<const int4*>(base + (size_t)idx0 * kRecordWords);
-    auto take = [&](uint32_t& pos) {
+    auto take = [&](uint32_t& pos, uint32_t& prim) {
         uint32_t n = 0;
         if (NQ == 1) {
             n = min(32u, rg.y - ce);
             pos = ce + sl;
+            prim = idx0;
             if (n) fetch(idx0);
             ce += n;
             idx0 = idx1;
@@ -594,14 +636,15 @@ __global__ __launch_bounds__(64, 6) void k_render_fwd(const ViewInfo* __restrict
             n = min(32u, qn);
             const uint2 e = queue[sl < n ? sl : 0u], rest = queue[min(32u + (uint32_t)lane, 95u)];
             pos = e.y;
-            if (n) fetch(sl < n ? e.x : 0u);
+            prim = sl < n ? e.x : 0u;
+            if (n) fetch(prim);
             qn -= n;
             __builtin_amdgcn_wave_barrier();
             if ((uint32_t)lane < qn) queue[lane] = rest;
         }
         return n;
     };
-    uint32_t pos, n_here = take(pos);
+    uint32_t pos, prim, n_here = take(pos, prim);
     while (n_here && live) {
         // which entries' rectangles meet each quad, from the first halves
         const float4 box = st[1];
@@ -634,8 +677,8 @@ __global__ __launch_bounds__(64, 6) void k_render_fwd(const ViewInfo* __restrict
         }
         const uint32_t mine_q = (row & 2) ? ((row & 1) ? m3 : m2) : ((row & 1) ? m1 : m0);
         uint32_t mask = ((uint32_t)(live >> (lane & 48)) & 0xffffu) ? mine_q : 0u;
-        uint32_t pos1;
-        n_here = take(pos1);
+        uint32_t pos1, prim1;
+        n_here = take(pos1, prim1);
         // inside the batch entries count from 0
         const uint32_t half0 = half, term0 = term;
         seen = ~0u;
@@ -647,6 +690,38 @@ __global__ __launch_bounds__(64, 6) void k_render_fwd(const ViewInfo* __restrict
             mask &= mask - 1u;
             w = words[(int)e * 16];
         };
+        if (EXACT) {
+            uint32_t any = m0 | m1 | m2 | m3;
+            const int most = max(max(__builtin_popcount(m0), __builtin_popcount(m1)),
+                                 max(__builtin_popcount(m2), __builtin_popcount(m3)));
+            if (any && __builtin_popcount(any) * kRowSteps <= most * kWaveSteps) {
+                mask = 0;
+                auto next_rec = [&](Rec& R) {
+                    const int b = __builtin_ctz(any);
+                    any &= any - 1u;
+                    load_rec<KIND>(base + (size_t)(uint32_t)__builtin_amdgcn_readlane((int)prim, b) * kRecordWords, R);
+                    return (uint32_t)b;
+                };
+                // Scalar loads complete out of order: wait for all in flight,
+                // then issue the next record's, then blend the one waited for.
+                Rec RA, RB;
+                uint32_t eA = next_rec(RA), eB = 0;
+                while (live) {
+                    smem_wait_all();
+                    const bool haveB = any != 0;
+                    if (haveB) eB = next_rec(RB);
+                    sched_fence();
+                    blend_together(RA, eA);
+                    if (!haveB || !live) break;
+                    smem_wait_all();
+                    const bool haveA = any != 0;
+                    if (haveA) eA = next_rec(RA);
+                    sched_fence();
+                    blend_together(RB, eB);
+                    if (!haveA) break;
+                }
+            }
+        }
         uint32_t eA, eB;
         float2 wA, wB;
         next(eA, wA);
@@ -672,6 +747,7 @@ __global__ __launch_bounds__(64, 6) void k_render_fwd(const ViewInfo* __restrict
             term = (term != ~0u) ? p_term + 1 : term0;
         }
         pos = pos1;
+        prim = prim1;
     }
     unsigned long long c_it = 0, c_ev = 0, c_hit = 0;
     if (valid) {
