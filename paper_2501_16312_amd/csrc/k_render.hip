@@ -58,6 +58,14 @@ __device__ inline void smem_wait_all() {
 }
 __device__ inline void sched_fence() { __builtin_amdgcn_sched_barrier(0); }
 
+// Between some lanes' LDS accesses and others' of the same wave.  LDS answers a
+// wave in order, so nothing has to be waited for, but the compiler knows of no
+// dependence between lanes, and accesses of different types it may reorder.
+__device__ inline void lds_hand_over() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
 __device__ inline int wave_max_int(int v) {
     for (int off = 32; off >= 1; off >>= 1) v = max(v, __shfl_xor(v, off, 64));
     return v;
@@ -632,15 +640,16 @@ __global__ __launch_bounds__(64, 6) void k_render_fwd(const ViewInfo* __restrict
                 if (ce < rg.y) rect = *reinterpret_cast<const int4*>(base + (size_t)idx0 * kRecordWords);
                 idx1 = chunk(ce + 64);
             }
-            __builtin_amdgcn_wave_barrier();
+            lds_hand_over();
             n = min(32u, qn);
             const uint2 e = queue[sl < n ? sl : 0u], rest = queue[min(32u + (uint32_t)lane, 95u)];
             pos = e.y;
             prim = sl < n ? e.x : 0u;
             if (n) fetch(prim);
             qn -= n;
-            __builtin_amdgcn_wave_barrier();
+            lds_hand_over();
             if ((uint32_t)lane < qn) queue[lane] = rest;
+            lds_hand_over();
         }
         return n;
     };
@@ -660,7 +669,7 @@ __global__ __launch_bounds__(64, 6) void k_render_fwd(const ViewInfo* __restrict
 #pragma unroll
         for (int k = 0; k < NH; ++k)
             if ((int)q0 + k < NQD) srec[sl][q0 + k] = st[k];
-        __builtin_amdgcn_wave_barrier();   // other lanes read what this one staged
+        lds_hand_over();   // other lanes read what this one staged
         if (kOutline) {
             const int steps = max(max(__builtin_popcount(m0), __builtin_popcount(m1)),
                                   max(__builtin_popcount(m2), __builtin_popcount(m3)));
@@ -732,7 +741,7 @@ __global__ __launch_bounds__(64, 6) void k_render_fwd(const ViewInfo* __restrict
             blend(wB, eB);
             next(eB, wB);
         }
-        __builtin_amdgcn_wave_barrier();
+        lds_hand_over();
         auto list_pos = [&](uint32_t e) {
             return (NQ == 1) ? (uint32_t)__builtin_amdgcn_readfirstlane((int)pos) + e : (uint32_t)__shfl((int)pos, (int)(e & 31u));
         };
@@ -1259,6 +1268,7 @@ __global__ __launch_bounds__(64) void k_render_bwd_rows(const ViewInfo* __restri
         const uint32_t m0 = (uint32_t)__ballot(qm & 1u), m1 = (uint32_t)__ballot(qm & 2u),
                        m2 = (uint32_t)__ballot(qm & 4u), m3 = (uint32_t)__ballot(qm & 8u);
         uint32_t mask = (row == 0) ? m0 : (row == 1) ? m1 : (row == 2) ? m2 : m3;
+        lds_hand_over();   // rows read, and add to, what other lanes staged
         while (true) {
             const bool act = mask != 0;
             if (__ballot(act) == 0) break;
@@ -1284,6 +1294,7 @@ __global__ __launch_bounds__(64) void k_render_bwd_rows(const ViewInfo* __restri
                 }
             }
         }
+        lds_hand_over();
         // the batch's records, one per lane
         if (meets) {
             const float4* acc4 = reinterpret_cast<const float4*>(sacc[lane]);
@@ -1291,6 +1302,7 @@ __global__ __launch_bounds__(64) void k_render_bwd_rows(const ViewInfo* __restri
 #pragma unroll
             for (int k = 0; k < kGradWords / 4; ++k) dst[k] = acc4[k];
         }
+        lds_hand_over();
     }
 }
 
