@@ -156,9 +156,11 @@ __device__ inline void ssim_rows(const float* __restrict__ X, const float* __res
         }
         // the tile's own pixels (zero beyond the image on both sides)
         if (r >= kSsimHalo && r < kSsimHalo + kLossTile) {
+            float run = 0.0f;
 #pragma unroll
             for (int q = 0; q < kRun; ++q)
-                if (INNER || x0 + c0 + q < W) l1 += fabsf(xv[8 + q] - yv[8 + q]);
+                if (INNER || x0 + c0 + q < W) run += fabsf(xv[8 + q] - yv[8 + q]);
+            l1 += run;
         }
 #pragma unroll
         for (int m = 0; m < 5; ++m)
@@ -205,7 +207,7 @@ __global__ __launch_bounds__(NT) void k_ssim_fwd(const float* __restrict__ rgb, 
                                                   float* __restrict__ partial, const uint32_t* __restrict__ skip) {
     if (skip && *skip) return;
     __shared__ __attribute__((aligned(16))) float hs[5][kRowsIn * kLossTile];
-    __shared__ float red[2][NT / 64];
+    __shared__ double red[2][NT / 64];
     const SsimTile tile = ssim_tile(W, H);
     if (!tile.valid) return;
     const int ch = tile.ch, x0 = tile.x0, y0 = tile.y0;
@@ -262,7 +264,10 @@ __global__ __launch_bounds__(NT) void k_ssim_fwd(const float* __restrict__ rgb, 
             ssum += sv;
         }
     }
-    // block sums, fixed order
+    // Block sums, in a fixed order: the waves' in float, as a tree; over the waves
+    // in double, rounded once.  One wave after the other in float would be further
+    // off than a tree over the block (one view of 65 x 97: 3.2e-8 of the loss, rms,
+    // against 2.1e-8).
     ssum = wave_sum_f(ssum);
     l1 = wave_sum_f(l1);
     if ((threadIdx.x & 63) == 0) {
@@ -271,11 +276,11 @@ __global__ __launch_bounds__(NT) void k_ssim_fwd(const float* __restrict__ rgb, 
     }
     __syncthreads();
     if (threadIdx.x < 2) {
-        const float* q = red[threadIdx.x];
-        float t = 0.0f;
+        const double* q = red[threadIdx.x];
+        double t = 0.0;
 #pragma unroll
         for (int w = 0; w < NT / 64; ++w) t += q[w];
-        partial[2 * tile.index + threadIdx.x] = t;
+        partial[2 * tile.index + threadIdx.x] = (float)t;
     }
 }
 
