@@ -27,9 +27,14 @@
  *     the linprim_camera array, the background colour and the outputs of
  *     linprim_pair_count / linprim_read_status, which are HOST pointers.
  *   - Calls only enqueue work on `stream` (a hipStream_t; NULL = the null
- *     stream) and return at once; none allocates device memory.  The single
- *     call that waits for the stream is linprim_pair_count (it must return a
- *     number to the host).
+ *     stream) and return at once; none allocates device memory.  Those that
+ *     return a number to the HOST wait for the stream: linprim_pair_count,
+ *     linprim_read_status, linprim_densify_plan, linprim_densify_noalloc,
+ *     linprim_mcmc_dead_count and linprim_loss_value.  They fail under stream
+ *     capture, and wherever HIP forbids to wait for the stream.  The first
+ *     wait of a process, other than linprim_densify_noalloc's and
+ *     linprim_loss_value's, allocates one page of pinned host memory, kept
+ *     until the process ends.
  *   - Return value: LINPRIM_OK (0) or a negative LINPRIM_ERR_* code; the
  *     outputs are then untouched.  linprim_strerror names the code.
  *   - Degenerate primitives (zero quaternion, a distance <= 0, non-finite

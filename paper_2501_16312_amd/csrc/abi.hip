@@ -1,6 +1,8 @@
 // abi.hip -- the extern "C" entry points of liblinprim.so: argument
 // validation, workspace layouts and launch order.  Every call enqueues on
-// the caller's stream; only linprim_pair_count / linprim_read_status wait.
+// the caller's stream; those that return a number to the host wait
+// (linprim_pair_count, linprim_read_status, linprim_densify_plan,
+// linprim_densify_noalloc, linprim_mcmc_dead_count, linprim_loss_value).
 #include <stddef.h>
 #include <stdlib.h>
 #include <string.h>

@@ -220,8 +220,8 @@ __global__ __launch_bounds__(NT) void k_ssim_fwd(const float* __restrict__ rgb, 
     else
         ssim_rows<NT, false>(X, Y, W, H, x0, y0, win, hs, l1);
     __syncthreads();
-    // column pass: a thread takes 4 neighbouring rows of one column
-    // (lanes run along a row, so the map stores are coalesced)
+    // column pass: a thread takes PER neighbouring rows of one column (4, or 2
+    // with eight waves; lanes run along a row, so the map stores are coalesced)
     {
         constexpr int PER = kLossTile * kLossTile / NT;
         const int c = threadIdx.x % kLossTile, r0 = (threadIdx.x / kLossTile) * PER;
@@ -303,7 +303,7 @@ __global__ __launch_bounds__(NT) void k_ssim_bwd(const float* __restrict__ rgb, 
     const float* X = rgb + ch * hw;
     const float* Y = target + ch * hw;
     float* G = grad + ch * hw;
-    // column pass: 4 neighbouring rows of one column per thread, the
+    // column pass: PER neighbouring rows of one column per thread, the
     // image's own pixels loaded before the barrier
     constexpr int PER = kLossTile * kLossTile / NT;
     const int c = threadIdx.x % kLossTile, r0 = (threadIdx.x / kLossTile) * PER;
@@ -361,8 +361,10 @@ SsimWindow ssim_window() {
 }
 
 // Up to two tiles per CU, a tile takes eight waves instead of four: the row
-// pass is one round instead of two, and nothing else waits for the waves (four
-// views of 288 x 229: 46 us against 52; at 1000 x 600, 3192 tiles, 74 against 67).
+// pass is one round instead of two, and nothing else waits for the waves.  Four
+// views, eight waves against four: 12 tiles a view (64 x 64) 40 us and 50, 216
+// 42 and 52, 480 54 and 61, 576 and 720 63 and 68, 900 78 and 77, 1824 (1000 x
+// 600) 128 and 123.  The line is where every CU has its two tiles at once.
 constexpr int64_t kSsimFewTiles = 512;
 
 // One view [3, H, W]: dmaps [3][3][H][W] scratch, partial [2 * 3 * tiles].

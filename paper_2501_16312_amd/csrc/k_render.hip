@@ -7,7 +7,8 @@
 //     pixel of its group;
 //   * forward: the list is taken 32 entries at a time with their records
 //     staged in LDS, and each 16-lane row of the wave walks the entries whose
-//     rectangle meets its 4 x 4 quad of the group;
+//     rectangle meets its 4 x 4 quad of the group (exact rays: the whole wave
+//     together where that takes hardly more steps);
 //   * backward: batches of 64 entries, one vector load brings 64 primitive
 //     indices and their pixel rectangles, a ballot keeps the entries whose
 //     rectangle meets the group, and only those entries' 32-dword payloads are
@@ -471,7 +472,6 @@ __device__ inline uint32_t quads_missed(const float* rec, float gx, float gy, fl
     const float margin = -0x1p-18f * m;
     return (least[0] < margin ? 1u : 0u) | (least[1] < margin ? 2u : 0u);
 }
-
 
 // Batches in which some quad's row has at least this many entries test the
 // outlines: the test costs a batch about four steps, and drops a third to a

@@ -26,7 +26,8 @@ constexpr int kGradWords = 20;            // backward record per (tile, primitiv
 
 // ----------------------------------------------------------------------------
 // Payload record of one (view, primitive), 32 dwords, written by the
-// preprocess kernel and read with scalar loads by the render kernels.
+// preprocess kernel.  The ray-space backward reads it with scalar loads, as does
+// the exact forward where the wave walks together; the others stage it in LDS.
 //   [0..3]  int   pixel rectangle i0, j0, i1, j1 (inclusive); i0 = -1 if culled
 //   [4]     float sigma * log2(e)            (so exp(-sigma d) = exp2(-s2 d))
 //   [5..7]  float rgb
@@ -97,11 +98,12 @@ struct ViewLayout {
 // Binning by tile counters (bin_sort's small path): up to this many tiles, one
 // block turns the counts into ranges and render orders, 1024 tiles a round.
 constexpr int64_t kPlanTiles = 8192;
-// ... and up to this many pairs (bin_sort, all launches, against emission, two
-// tile-bit radix passes, ranges and orders): 18k pairs 22 us against 41, 64k 32
-// against 43, 81k 35 against 49, 103k (most in runs of many tiles) 50 against
-// 50; with an atomic per pair instead of one per block and tile, 220k pairs
-// took 57 us of kernel time against 43.
+// ... and up to this many pairs (bin_sort, all launches, against emission,
+// tile-bit radix passes, ranges and orders): 16k pairs 24 us against 41, 54k 26
+// against 44, 90k 34 against 45, 108k 36 against 51; in runs of many tiles, 21k
+// 31 against 67, 113k 31 against 68.  Still ahead at the limit; beyond, not
+// measured as it stands (with 64 slots to a wave 149k short runs 37 against 52,
+// 158k long ones 152 against 70).
 constexpr int64_t kPlacePairs = 131072;
 inline int64_t counted_tiles(int64_t n_tiles) { return n_tiles <= kPlanTiles ? n_tiles : 0; }
 
