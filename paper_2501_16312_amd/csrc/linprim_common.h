@@ -202,7 +202,10 @@ __host__ __device__ inline uint2 pack_tile_rect(int i0, int j0, int i1, int j1, 
 // walks start first and the waves that start last are short (the exact
 // variant's forward takes it too).  The ray-space forward's:
 // groups of consecutive classes (the last class of each group in
-// kFwdGroupLast), each group in tile order.
+// kFwdGroupLast), each group in tile order.  Forward of 1M octahedra of a room, of
+// 16 views of 500k and of a 300k view at 16-pixel tiles: these three groups 63,
+// 322 and 36 us; one 82, 328 and 41; the backward's classes 63, 340 and 36.  Exact
+// rays, 300k: 47 in the three groups, 42 in the classes.
 constexpr int kOrderClasses = 16;
 __device__ constexpr uint32_t kOrderBounds[kOrderClasses - 1] = {192, 128, 96, 72, 56, 48, 40, 32,
                                                                  26, 20, 16, 12, 8, 4, 0};
