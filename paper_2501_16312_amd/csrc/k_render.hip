@@ -418,7 +418,12 @@ constexpr float kDepthT = 0.5f;
 // instructions (46 with a select for the empty mask and entries counted from 1)
 // against 39 of the wave-uniform walk (20k octahedra 0.05-0.3 wide at 1080p,
 // 8-pixel tiles: 57 us, now 59; 20k tetrahedra 76 and 79).
-// Wider tiles first filter the list for the group, so that batches are full.
+// Wider tiles first filter the list for the group, so that batches are full; a
+// list of one batch is not filtered, which saves a sparse image a load and an
+// LDS round trip per group (20k octahedra of a room at 3840 x 2160, 16-pixel
+// tiles: 70 us filtered, 57 so, 57 before the quads; exact rays 75, 64 and 59;
+// 16 views of 500k 417 and 387).  Seven waves per SIMD, but for depth maps at
+// wide tiles, which would spill.
 __device__ inline double centre_depth(const ViewInfo& V, const float* __restrict__ means, uint32_t prim, bool exact) {
     const double x = means[3 * (size_t)prim], y = means[3 * (size_t)prim + 1], z = means[3 * (size_t)prim + 2];
     const double t0 = V.Rw[0] * x + V.Rw[1] * y + V.Rw[2] * z + V.tw[0];
@@ -498,7 +503,7 @@ constexpr int kOutlineSteps = 20;
 constexpr int kRowSteps = 8, kWaveSteps = 9;
 
 template <int TILE, int KIND, bool COUNT, bool EXACT, bool DEPTH>
-__global__ __launch_bounds__(64, 6) void k_render_fwd(const ViewInfo* __restrict__ views, int n_views, int64_t n,
+__global__ __launch_bounds__(64, (DEPTH && TILE > 8) ? 6 : 7) void k_render_fwd(const ViewInfo* __restrict__ views, int n_views, int64_t n,
                                                    const float* __restrict__ payload, const uint32_t* __restrict__ vals,
                                                    const uint2* __restrict__ ranges, const Status* __restrict__ status,
                                                    uint64_t capacity, float bg0, float bg1, float bg2,
@@ -606,27 +611,29 @@ __global__ __launch_bounds__(64, 6) void k_render_fwd(const ViewInfo* __restrict
     const float2* words = reinterpret_cast<const float2*>(srec[0]) + li;
     // The next up to 32 entries that meet the group: their number, their list
     // positions and primitives (lane l: entry l & 31), their records on the way.
-    // A group-sized tile takes its list as it is; others filter it, 64 entries at
-    // a time.
-    constexpr uint32_t CH = (NQ == 1) ? 32 : 64;
+    // A group-sized tile takes its list as it is, and so does a list of one batch
+    // (the quads' masks leave out what does not meet the group); others are
+    // filtered, 64 entries at a time.
+    const bool whole = NQ == 1 || rg.y - rg.x <= 32u;
     uint32_t ce = rg.x, qn = 0;
     auto chunk = [&](uint32_t e) {
-        const uint32_t k = (NQ == 1) ? sl : (uint32_t)lane;
+        const uint32_t k = whole ? sl : (uint32_t)lane;
         return (e < rg.y && k < rg.y - e) ? vals[e + k] : 0u;
     };
-    uint32_t idx0 = chunk(ce), idx1 = chunk(ce + CH);
+    uint32_t idx0 = chunk(ce), idx1 = chunk(ce + (NQ == 1 ? 32u : 64u));
     int4 rect = make_int4(0, 0, 0, 0);
-    if (NQ > 1) rect = *reinterpret_cast<const int4*>(base + (size_t)idx0 * kRecordWords);
+    if (!whole) rect = *reinterpret_cast<const int4*>(base + (size_t)idx0 * kRecordWords);
     auto take = [&](uint32_t& pos, uint32_t& prim) {
         uint32_t n = 0;
-        if (NQ == 1) {
+        if (whole) {
             n = min(32u, rg.y - ce);
             pos = ce + sl;
             prim = idx0;
-            if (n) fetch(idx0);
             ce += n;
-            idx0 = idx1;
-            idx1 = chunk(ce + 32);
+            if (NQ == 1) {
+                idx0 = idx1;
+                idx1 = chunk(ce + 32);
+            }
         } else {
             while (qn < 32 && ce < rg.y) {
                 const bool rel = (uint32_t)lane < rg.y - ce && rect_meets_group(rect, P.gx0, P.gy0);
@@ -645,12 +652,12 @@ __global__ __launch_bounds__(64, 6) void k_render_fwd(const ViewInfo* __restrict
             const uint2 e = queue[sl < n ? sl : 0u], rest = queue[min(32u + (uint32_t)lane, 95u)];
             pos = e.y;
             prim = sl < n ? e.x : 0u;
-            if (n) fetch(prim);
             qn -= n;
             lds_hand_over();
             if ((uint32_t)lane < qn) queue[lane] = rest;
             lds_hand_over();
         }
+        if (n) fetch(prim);
         return n;
     };
     uint32_t pos, prim, n_here = take(pos, prim);
